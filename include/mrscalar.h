@@ -179,7 +179,15 @@ int mr_divergence(mr_ctx* ctx, const void* u, const void* v, const void* w,
  *   otherwise (leapfrog):      tau = 2 dt,   a_p = 1,   a_c = 0,   lag = n-1.
  * th_prev is not read at n = 0 (may be NULL).  th_next must not alias th_prev or
  * th_cur: callers rotate three buffers.  The tridiagonal elimination runs in
- * double for both precisions.  One fused line-solver kernel, or with
+ * double for both precisions.  With step_method 0, x and y periodic with
+ * uniform widths and the plain method, the step is one streaming kernel where
+ * that is the fastest form (FP64 with an even N_x, or 4.5e6 cells and more, or
+ * columns taller than 640 levels) and the z system allows it: it back-
+ * substitutes over a limited look-ahead, at most 60 levels, past which the
+ * values left out enter the solution with a share below 7e-18 (FP64) or 1e-14
+ * (FP32), less than the rounding of the stored type.  (A column that holds a
+ * NaN or Inf therefore becomes non-finite from its look-ahead below, not whole,
+ * in one step.)  Otherwise one fused line-solver kernel, or with
  * step_method 2 (and on columns taller than 640 levels) one column sweep and
  * its back substitution (see mr_scalar_steps). */
 int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_cur, void* th_next,
@@ -191,8 +199,9 @@ int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_c
  * the two levels before it (outs[0] from th_cur and th_prev, outs[1] from
  * outs[0] and th_cur, outs[q] from outs[q-1] and outs[q-2]): a ring of three
  * buffers satisfies this.  Results equal count calls of mr_scalar_step to
- * rounding.
- * With step_method 2, and with step_method 0 on grids whose sweep tiles keep
+ * rounding.  Where mr_scalar_step is one streaming kernel, so is each step here
+ * (nothing is allocated).  Otherwise:
+ * with step_method 2, and with step_method 0 on grids whose sweep tiles keep
  * the GPU full (at least 16 wavefronts per CU, rounds of tiles at least 3/4
  * full: 576 x 576 and 1024 x 1024 columns, not 256 x 256) or columns too tall
  * for the line solver (x and y periodic with uniform widths and the plain
@@ -222,7 +231,9 @@ int mr_adjoint_seed(mr_ctx* ctx, int64_t n, const void* lam, void* mu_out, void*
  * n == 0: out = dL/dtheta^0 = lam^0 + tau_0 kappa Lh^T mu^0 (the start-up step
  *         reads theta^0 for its diffusion too).
  * out must not alias the inputs.  Velocity gradients are accumulated
- * separately by mr_velocity_grad.  On columns taller than the line solver's
+ * separately by mr_velocity_grad.  Where mr_scalar_step is one streaming kernel,
+ * so is the reverse step with n >= 1 and no lam_add.  Otherwise, on columns
+ * taller than the line solver's
  * the step runs as a column sweep (n >= 1: a sweep and a back substitution;
  * n = 0: one pass with no solve); lam_add is then refused (MR_ESHAPE). */
 int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const void* mu_cur,
@@ -237,7 +248,8 @@ int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const v
  * Every output must differ from the two levels before it (outs[0] from
  * mu_cur and mu_next, outs[1] from outs[0] and mu_cur, outs[q] from outs[q-1]
  * and outs[q-2]).  Results equal count calls of mr_scalar_step_backward to
- * rounding.  Where the context runs step sequences as column sweeps
+ * rounding.  Where mr_scalar_step is one streaming kernel, so is each reverse
+ * step here.  Otherwise, where the context runs step sequences as column sweeps
  * (mr_get_step_method 2) the reverse steps run as column sweeps too: each
  * kernel back-substitutes the previous reverse step's transposed solve while
  * it eliminates its own the other way (7 values per cell and step), with the
@@ -377,7 +389,8 @@ int mr_host_z_face_weights(const mr_desc* desc, double* w_out);
 int mr_host_face_weights(const mr_desc* desc, int32_t axis, double* w_out);
 
 /* The method mr_scalar_steps uses on this context: 1 = the fused line
- * solver, 2 = column sweeps. */
+ * solver, 2 = column sweeps.  With step_method 0 the streaming step may stand
+ * in for either (see mr_scalar_step). */
 int mr_get_step_method(const mr_ctx* ctx, int32_t* method);
 
 /* Dense sizes of a context and its precision. */

@@ -1,0 +1,174 @@
+// Host side of the streaming step: how a context's grid is cut into tiles and
+// z segments, and the launches (kernels in stream_kernel.h, instantiated in
+// k_stream64.hip and k_stream32.hip).
+#include "stream_kernel.h"
+
+#include <algorithm>
+
+namespace mr {
+namespace stream {
+extern template hipError_t launch_stream<double, false>(int, int, dim3, const StreamArgs<double>&, hipStream_t);
+extern template hipError_t launch_stream<double, true>(int, int, dim3, const StreamArgs<double>&, hipStream_t);
+extern template hipError_t launch_stream<float, false>(int, int, dim3, const StreamArgs<float>&, hipStream_t);
+extern template hipError_t launch_stream<float, true>(int, int, dim3, const StreamArgs<float>&, hipStream_t);
+}  // namespace stream
+
+// Tile shape and number of z segments: the pair with the least time by a model
+// of what bounds the launch, the longer of
+//   - the bytes of all workgroups at the rate that the shape reaches when the
+//     GPU is full (wider rows of columns do better), half of the columns past a
+//     ragged end counted;
+//   - the levels of a walk times what a level takes a CU that holds one
+//     workgroup, or as many as the fullest CU gets.
+// Timed, for instance (128 x 4 columns: 256^3 in FP64, 144 us with 2 segments,
+// one workgroup for each of 256 CUs; 185 us with 1, 180 with 3, half of the CUs
+// idle or a second round for half of them).  400^3 FP64: 256 x 4 and 1 segment
+// 587 us, 128 x 4 692; 576^3 FP64: 192 x 4 1.83 ms, 256 x 4 2.06; 450 x 300 x
+// 200 FP32: 192 x 4 154 us, 128 x 4 183 (300 workgroups on 256 CUs).
+StreamPlan stream_plan(int nx, int ny, int nz, bool f64, int cus, int depth, const std::vector<int> (&before)[2],
+                       const std::vector<int> (&after)[2]) {
+  struct Shape {
+    double one_us;    // a level of the only workgroup of a CU
+    double more_us;   // a level for each workgroup of a CU that holds several
+    double rate;      // bytes per us of a full GPU
+  };
+  static const Shape s64[kStreamShapes] = {{1.40, 1.40, 5.6e6}, {1.13, 1.13, 5.5e6}, {0.72, 0.72, 5.35e6}, {0.60, 0.33, 5.0e6}};
+  static const Shape s32[kStreamShapes] = {{0.70, 0.70, 5.6e6}, {0.70, 0.60, 5.5e6}, {0.61, 0.38, 5.35e6}, {0.55, 0.25, 5.0e6}};
+  const Shape* sh = f64 ? s64 : s32;
+  const double sz = f64 ? 8.0 : 4.0;
+  StreamPlan best;
+  double best_us = -1.0;
+  for (int q = 0; q < kStreamShapes; ++q) {
+    if (!stream_fits(kStreamDepth[depth], kStreamShape[q].segs * kStreamShape[q].rows)) continue;
+    const int tw = 64 * kStreamShape[q].segs, rows = kStreamShape[q].rows;
+    const int64_t ntx = (nx + tw - 1) / tw, nty = (ny + rows - 1) / rows;
+    const double cols = (double)nx * ny;
+    const double loaded = cols + 0.5 * ((double)(ntx * tw) * (nty * rows) - cols);
+    for (int nseg = 1; nseg <= kStreamMaxSeg && (nseg == 1 || nz / nseg >= 8); ++nseg) {
+      StreamPlan p;
+      p.shape = q;
+      p.nseg = nseg;
+      int levels = 0;
+      double walked = 0.0;
+      for (int d = 0; d < 2; ++d)
+        for (int g = 0; g < nseg; ++g) {
+          const int ks = (int)((int64_t)nz * g / nseg), ke = (int)((int64_t)nz * (g + 1) / nseg);
+          const int a0 = g ? std::max(0, ks - before[d][ks]) : 0;
+          int a1 = std::min(nz, ke + after[d][ke - 1]);
+          a1 += (kStreamBlock - (a1 - a0) % kStreamBlock) % kStreamBlock;   // whole blocks
+          p.seg[d].insert(p.seg[d].end(), {ks, ke, a0, a1});
+          levels = std::max(levels, a1 - a0);
+          if (d == 0) walked += a1 - a0;
+        }
+      const double per_cu = (double)((ntx * nty * nseg + cus - 1) / cus);   // of the fullest CU
+      const double mem = (5.0 * walked + nz) * loaded * sz / sh[q].rate;
+      const double us = std::max(mem, (levels + 6) * std::max(sh[q].one_us, per_cu * sh[q].more_us));
+      if (best_us < 0.0 || us < best_us) {
+        best_us = us;
+        best = p;
+      }
+    }
+  }
+  return best;
+}
+
+namespace {
+using namespace stream;
+
+template <typename T>
+const StreamSys<T>& sys(const mr_ctx* c, bool rev, int down, int kind);
+template <>
+const StreamSys<double>& sys<double>(const mr_ctx* c, bool rev, int down, int kind) { return c->sr64[rev][down][kind]; }
+template <>
+const StreamSys<float>& sys<float>(const mr_ctx* c, bool rev, int down, int kind) { return c->sr32[rev][down][kind]; }
+
+// Arguments of both directions: f the advected field, p the second field, the
+// implicit system of step kind `solve` (transposed in the reverse step).
+template <typename T, bool REV>
+StreamArgs<T> base_args(const mr_ctx* c, bool down, int solve, const void* f, const void* p, void* out, const void* u,
+                        const void* v, const void* w) {
+  StreamArgs<T> a;
+  ::memset((void*)&a, 0, sizeof(a));
+  a.f = (const T*)f;
+  a.p = (const T*)p;
+  a.u = (const T*)u;
+  a.v = (const T*)v;
+  a.w = (const T*)w;
+  a.out = (T*)out;
+  a.down = down;
+  a.row = sys<T>(c, REV, a.down, solve).row;
+  a.cb = sys<T>(c, REV, a.down, solve).cb;
+  a.seg = c->stream_seg[a.down];
+  a.uhx = (T)c->uhx;
+  a.uhy = (T)c->uhy;
+  a.uxx = (T)(c->uhx * c->uhx);
+  a.uyy = (T)(c->uhy * c->uhy);
+  a.nx = c->nx;
+  a.ny = c->ny;
+  a.nz = c->nz;
+  const StreamShape sh = kStreamShape[c->stream_shape];
+  a.ntx = (c->nx + 64 * sh.segs - 1) / (64 * sh.segs);
+  a.nty = (c->ny + sh.rows - 1) / sh.rows;
+  // bands of 8 x tiles: 1024 x 1024 x 512 within 1% of 4, 2-6% faster than 1 and 2
+  a.band = std::min(8, a.ntx);
+  return a;
+}
+
+template <typename T, bool REV>
+hipError_t launch(const mr_ctx* c, const StreamArgs<T>& a, hipStream_t s) {
+  const dim3 grid((unsigned)((int64_t)a.ntx * a.nty * c->stream_nseg));
+  return launch_stream<T, REV>(c->stream_shape, c->stream_d - 1, grid, a, s);
+}
+
+template <typename T>
+hipError_t fwd_t(mr_ctx* c, int64_t n, int q, const void* thp, const void* thc, void* out, const void* u, const void* v,
+                 const void* w, hipStream_t s) {
+  const int kind = step_kind(n, c->n_avg);
+  // FP32 where the column sweeps would run (q >= 0, the step's index in its
+  // sequence): their walk direction and their float elimination values, so that
+  // the same float results come out (but for the last bit where the doubles
+  // behind them differ in theirs)
+  const bool as_sweep = sizeof(T) == 4 && q >= 0;
+  StreamArgs<T> a = base_args<T, false>(c, as_sweep ? !(q & 1) : (n & 1), kind, thc, thp, out, u, v, w);
+  a.as_sweep = as_sweep;
+  a.ap = (T)alpha_prev(kind);
+  a.ac = (T)alpha_cur(kind);
+  a.tau = (T)c->tau[kind];
+  a.tk = (T)(c->tau[kind] * c->kappa);
+  return launch<T, false>(c, a, s);
+}
+
+// Reverse step n >= 1: the transposed stencils of step n on mu^n, the lagged
+// diffusion of step n+1 on mu^{n+1} (zero weights without one), the transposed
+// system of step n-1.
+template <typename T>
+hipError_t bwd_t(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* out, const void* u, const void* v,
+                 const void* w, hipStream_t s) {
+  const int kind = step_kind(n, c->n_avg);
+  StreamArgs<T> a =
+      base_args<T, true>(c, n & 1, step_kind(n - 1, c->n_avg), muc, mun ? mun : muc, out, u, v, w);
+  a.ac = (T)alpha_cur(kind);
+  a.tau = (T)c->tau[kind];
+  if (mun) {
+    const int k1 = step_kind(n + 1, c->n_avg);
+    a.ap = (T)alpha_prev(k1);
+    a.tk = (T)(c->tau[k1] * c->kappa);
+  }
+  return launch<T, true>(c, a, s);
+}
+
+}  // namespace
+
+hipError_t launch_stream_step(mr_ctx* c, int64_t n, int q, const void* thp, const void* thc, void* out,
+                              const void* u, const void* v, const void* w, hipStream_t s) {
+  return c->precision == MR_FP64 ? fwd_t<double>(c, n, q, thp, thc, out, u, v, w, s)
+                                 : fwd_t<float>(c, n, q, thp, thc, out, u, v, w, s);
+}
+
+hipError_t launch_stream_step_backward(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* out,
+                                       const void* u, const void* v, const void* w, hipStream_t s) {
+  return c->precision == MR_FP64 ? bwd_t<double>(c, n, mun, muc, out, u, v, w, s)
+                                 : bwd_t<float>(c, n, mun, muc, out, u, v, w, s);
+}
+
+}  // namespace mr

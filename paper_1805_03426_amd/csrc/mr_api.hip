@@ -363,6 +363,77 @@ bool sweep_factors(int nz, const double* sub, const double* diag, const double* 
   return true;
 }
 
+// Number of walk positions after position s whose values still matter to the
+// solution at s (and before it, whose elimination values do): the shortest
+// distance over which the product of the recurrence's factors falls to eps.
+int reach_ahead(const vector<double>& cb, int s, double eps) {
+  const int n = (int)cb.size();
+  double p = 1.0;
+  int d = 0;
+  while (s + d < n && p > eps) p *= fabs(cb[s + d++]);
+  return d;
+}
+int reach_behind(const vector<double>& a, int s, double eps) {
+  double p = 1.0;
+  int d = 0;
+  while (s - d >= 0 && p > eps) p *= fabs(a[s - d++]);
+  return d;
+}
+
+// One system's streaming tables in one walk direction, by walk position.
+struct StreamHost {
+  vector<double> m, a, cb;
+};
+StreamHost stream_walk(const SweepHost& h, bool down) {
+  StreamHost w;
+  w.m = down ? h.dn_m : h.up_m;
+  w.a = down ? h.dn_a : h.up_a;
+  w.cb = down ? h.dn_cb : h.up_cb;
+  // the downward factors pair with an upward back substitution: theta_k = e_k - dn_cb_k theta_{k-1}
+  if (down)
+    for (vector<double>* v : {&w.m, &w.a, &w.cb}) std::reverse(v->begin(), v->end());
+  return w;
+}
+
+template <typename T>
+vector<mr::StreamRow<T>> stream_rows(const Axis& z, const SweepHost& h, const StreamHost& walk, bool rev, bool down) {
+  const int nz = z.n;
+  vector<mr::StreamRow<T>> r((size_t)nz + 2 * mr::kStreamRowPad);
+  memset((void*)r.data(), 0, r.size() * sizeof(r[0]));
+  for (int s = 0; s < nz; ++s) {
+    const int k = down ? nz - 1 - s : s;
+    mr::StreamRow<T>& o = r[(size_t)s + mr::kStreamRowPad];
+    o.em = walk.m[s];
+    o.ea = walk.a[s];
+    o.tkb = h.tkb[k];
+    // 1/hz of this level, of the one below and of the one above (0: a wall)
+    const double ih = 1.0 / z.h[k], ihl = k > 0 ? 1.0 / z.h[k - 1] : 0.0, ihh = k < nz - 1 ? 1.0 / z.h[k + 1] : 0.0;
+    const double lo = k > 0 ? ih : 0.0, hi = k < nz - 1 ? ih : 0.0;
+    if (rev) {
+      o.c0 = (T)(down ? -ihl : ihh);
+      o.c1 = (T)(down ? -lo : hi);
+      o.c2 = (T)(down ? -hi : lo);
+      o.c3 = (T)(down ? -ihh : ihl);
+    } else {
+      if (sizeof(T) == 8) {
+        o.c0 = (T)(down ? -lo : hi);
+        o.c2 = (T)(down ? hi : -lo);
+      } else {
+        o.c0 = (T)((down ? lo : hi) != 0.0);
+        o.c1 = (T)ih;
+        o.c2 = (T)((down ? hi : lo) != 0.0);
+      }
+    }
+  }
+  return r;
+}
+
+vector<double> stream_cb(const StreamHost& w) {
+  vector<double> cb(w.cb.size() + 2 * mr::kStreamPad, 0.0);
+  std::copy(w.cb.begin(), w.cb.end(), cb.begin() + mr::kStreamPad);
+  return cb;
+}
+
 // Shortest chunk length that splits nz levels into at most
 // kMaxChunks chunks.
 int choose_chunks(int nz, int& L, int& nch) {
@@ -661,6 +732,25 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   SweepOffsets swo[mr::NKINDS], swto[mr::NKINDS];
   double taus[mr::NKINDS];
   const int nz = P.z.n;
+  const bool f64 = desc->precision == MR_FP64;
+  size_t sro[2][2][mr::NKINDS], scbo[2][2][mr::NKINDS];   // streaming tables: [transposed][down][kind]
+  const double eps = f64 ? mr::kTruncate64 : mr::kTruncate32;
+  int ahead = 0;                                      // the streaming step's look-ahead
+  vector<int> after[2], before[2];                    // its reach after / before each walk position
+  for (int d = 0; d < 2; ++d) after[d].assign(nz, 0), before[d].assign(nz, 0);
+  auto pack_stream = [&](const SweepHost& h, int kind, bool rev) {
+    if (!P.sweep_ok || desc->step_method != 0) return;
+    for (int d = 0; d < 2; ++d) {
+      const StreamHost w = stream_walk(h, d);
+      sro[rev][d][kind] = f64 ? pk.put(stream_rows<double>(P.z, h, w, rev, d)) : pk.put(stream_rows<float>(P.z, h, w, rev, d));
+      scbo[rev][d][kind] = pk.put(stream_cb(w));
+      for (int k = 0; k < nz; ++k) {
+        after[d][k] = std::max(after[d][k], reach_ahead(w.cb, k, eps));
+        before[d][k] = std::max(before[d][k], reach_behind(w.a, k, eps));
+        ahead = std::max(ahead, after[d][k]);
+      }
+    }
+  };
   vector<double> sub(nz), diag(nz), sup(nz), bz(nz), tsub(nz), tsup(nz);
   for (int kind = 0; kind < mr::NKINDS; ++kind) {
     const double tau = kind_tau(kind, desc->dt);
@@ -673,6 +763,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     sh.tkb.assign(nz, 0.0);
     for (int k = 0; k < nz; ++k) sh.tkb[k] = tk * bz[k];
     swo[kind] = pack_sweep(pk, sh);
+    pack_stream(sh, kind, false);
     // transpose: sub^T_k = sup_{k-1}, sup^T_k = sub_{k+1}
     for (int k = 0; k < nz; ++k) {
       tsub[k] = k > 0 ? sup[k - 1] : 0.0;
@@ -682,6 +773,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     if (!sweep_factors(nz, tsub.data(), diag.data(), tsup.data(), sht)) return MR_EINVAL;
     sht.tkb.assign(nz, 0.0);
     swto[kind] = pack_sweep(pk, sht);
+    pack_stream(sht, kind, true);
     if (nch == 0) continue;
     ZHost zh, th;
     if (!z_factors(nz, L, sub.data(), diag.data(), sup.data(), zh)) return MR_EINVAL;
@@ -699,6 +791,24 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   shid.up_cb.assign(nz, 0.0); shid.dn_cb.assign(nz, 0.0);
   shid.tkb.assign(nz, 0.0);
   const SweepOffsets swido = pack_sweep(pk, shid);
+  // the streaming step's look-ahead, tiles and z segments.  It runs wherever it
+  // applies but on small grids whose copies into LDS are of 4 bytes (FP64, odd
+  // N_x) and on small FP32 grids, where the line solver is faster: FP64 127^3
+  // 38 us against 54, 175^3 105 against 86; FP32 128^3 19.5 us against 24, 160^3
+  // 31 against 36, 176^3 53 against 41, 175^3 58 against 52
+  const bool streams = nch == 0 || (f64 && P.x.n % 2 == 0) || (int64_t)P.x.n * P.y.n * nz >= 4500000;
+  int cus = 0, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    cus = 256;
+  int stream_d = 0;
+  mr::StreamPlan plan;
+  if (P.sweep_ok && desc->step_method == 0 && streams) {
+    for (int d = mr::kStreamDepths; d > 0; --d)
+      if (ahead <= mr::kStreamDepth[d - 1]) stream_d = d;
+    if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, cus, stream_d - 1, before, after);
+  }
+  const size_t o_seg[2] = {pk.put(plan.seg[0]), pk.put(plan.seg[1])};
   vector<double> dcz(P.z.dc);
   size_t o_hx64 = pk.put(P.x.h), o_hy64 = pk.put(P.y.h), o_dcz = pk.put(dcz), o_hz64 = pk.put(P.z.h);
 
@@ -763,10 +873,6 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   // the line solver is 2.7x (FP64) and 2.5x (FP32) faster; at 576^3 (432
   // tiles of 192 x 4) the sweeps are 10% and 20% faster; at 1024 x 1024 x 512
   // (1024 tiles) 27% and 25% faster.
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1)
-    cus = 256;
-  const bool f64 = c->precision == MR_FP64;
   c->sweep_shape = desc->sweep_tile > 0 ? desc->sweep_tile - 1 : mr::sweep_pick_shape(c->nx, f64);
   const mr::SweepShape sh = mr::kSweepShape[c->sweep_shape];
   const int tw = 64 * sh.segs;
@@ -775,6 +881,17 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   const bool fills = tiles * sh.segs * sh.rows >= 16 * (int64_t)cus && (rounds == 1 || 4 * tiles >= 3 * rounds * slots);
   c->sweep_pref = desc->step_method == 2 || (desc->step_method == 0 && P.sweep_ok && (nch == 0 || fills));
   c->sweep_single = nch == 0 || desc->step_method == 2;
+  c->stream_d = stream_d;
+  c->stream_shape = plan.shape;
+  c->stream_nseg = plan.nseg;
+  for (int d = 0; d < 2; ++d) c->stream_seg[d] = (const int*)(base + o_seg[d]);
+  for (int k = 0; k < mr::NKINDS && stream_d; ++k)
+    for (int r = 0; r < 2; ++r)
+      for (int d = 0; d < 2; ++d) {
+        const double* cb = (const double*)(base + scbo[r][d][k]) + mr::kStreamPad;
+        c->sr64[r][d][k] = {(const mr::StreamRow<double>*)(base + sro[r][d][k]) + mr::kStreamRowPad, cb};
+        c->sr32[r][d][k] = {(const mr::StreamRow<float>*)(base + sro[r][d][k]) + mr::kStreamRowPad, cb};
+      }
   c->hx64 = (const double*)(base + o_hx64);
   c->areaw = (const double*)(base + o_hy64);
   c->dcz = (const double*)(base + o_dcz);
@@ -832,6 +949,11 @@ int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_c
   if (n > 0 && !th_prev) return MR_EINVAL;
   if (th_next == th_cur || th_next == th_prev) return MR_EINVAL;
   const void* thp = n > 0 ? th_prev : th_cur;
+  if (ctx->stream_d) {
+    MR_LAUNCH(mr::launch_stream_step(ctx, n, ctx->sweep_single ? 0 : -1, thp, th_cur, th_next, u, v, w,
+                                     as_stream(stream)));
+    return MR_OK;
+  }
   if (ctx->sweep_single) {
     // one column sweep and its back substitution
     void* outs[1] = {th_next};
@@ -855,6 +977,14 @@ int mr_scalar_steps(mr_ctx* ctx, int64_t n0, int32_t count, const void* th_prev,
     if (!outs[q] || outs[q] == l1 || outs[q] == l2) return MR_EINVAL;
   }
   hipStream_t s = as_stream(stream);
+  if (ctx->stream_d) {
+    for (int32_t q = 0; q < count; ++q) {
+      const void* a = q >= 2 ? outs[q - 2] : (q == 1 ? th_cur : thp);
+      const void* b = q >= 1 ? outs[q - 1] : th_cur;
+      MR_LAUNCH(mr::launch_stream_step(ctx, n0 + q, ctx->sweep_pref ? q : -1, a, b, outs[q], u, v, w, s));
+    }
+    return MR_OK;
+  }
   if (ctx->sweep_pref) {
     MR_LAUNCH(mr::launch_sweep_steps(ctx, n0, count, thp, th_cur, outs, u, v, w, s));
     return MR_OK;
@@ -885,6 +1015,10 @@ int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const v
   MR_CALL_RANGE();
   if (!ctx || n < 0 || !mu_cur || !out || !u || !v || !w) return MR_EINVAL;
   if (out == mu_cur || (mu_next && out == mu_next) || (lam_add && out == lam_add)) return MR_EINVAL;
+  if (ctx->stream_d && n > 0 && !lam_add) {
+    MR_LAUNCH(mr::launch_stream_step_backward(ctx, n, mu_next, mu_cur, out, u, v, w, as_stream(stream)));
+    return MR_OK;
+  }
   if (ctx->nch == 0) {
     // columns beyond the line solver: the reverse step as a column sweep
     // and its back substitution (no lam_add there)
@@ -914,6 +1048,14 @@ int mr_scalar_steps_backward(mr_ctx* ctx, int64_t n0, int32_t count, const void*
     if (!outs[q] || outs[q] == l1 || outs[q] == l2) return MR_EINVAL;
   }
   hipStream_t s = as_stream(stream);
+  if (ctx->stream_d) {
+    for (int32_t q = 0; q < count; ++q) {
+      const void* nxt = q >= 2 ? outs[q - 2] : (q == 1 ? mu_cur : mu_next);
+      const void* cur = q >= 1 ? outs[q - 1] : mu_cur;
+      MR_LAUNCH(mr::launch_stream_step_backward(ctx, n0 - q, nxt, cur, outs[q], u, v, w, s));
+    }
+    return MR_OK;
+  }
   if (ctx->sweep_pref) {
     MR_LAUNCH(mr::launch_sweep_bwd_steps(ctx, n0, count, mu_next, mu_cur, outs, u, v, w, s));
     return MR_OK;
@@ -1014,7 +1156,7 @@ int mr_coarse_step(mr_ctx* ctx, int64_t n0, int32_t mt, const void* U0, const vo
     return MR_EINVAL;
   if (n0 == 0) p = c;
   hipStream_t s = as_stream(stream);
-  if (ctx->sweep_pref) {
+  if (ctx->sweep_pref && !ctx->stream_d) {
     // column sweeps: the kernel of sub-step i finishes theta^{n0+i-1} and
     // starts sub-step i on the velocity refined just before it (the velocity
     // at the start of the sub-step, fraction (i-1)/mt)
@@ -1043,7 +1185,9 @@ int mr_coarse_step(mr_ctx* ctx, int64_t n0, int32_t mt, const void* U0, const vo
       const int64_t n = n0 + i - 1;
       int o = 0;
       while (o == c || o == p) ++o;   // the buffer holding neither level
-      MR_LAUNCH(mr::launch_step(ctx, n, ring[p], ring[c], ring[o], u, v, w, s));
+      MR_LAUNCH(ctx->stream_d ? mr::launch_stream_step(ctx, n, ctx->sweep_pref ? i - 1 : -1, ring[p], ring[c], ring[o], u,
+                                                       v, w, s)
+                              : mr::launch_step(ctx, n, ring[p], ring[c], ring[o], u, v, w, s));
       p = c;
       c = o;
     }

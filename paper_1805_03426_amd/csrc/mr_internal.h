@@ -100,6 +100,62 @@ struct SweepSys {
   const double* tkb;
 };
 
+// Streaming step: the look-aheads its kernels are compiled for, the levels per
+// block of its walk (blocks of 4 were 3-4% slower), the readable positions
+// before the first and after the last of its row and back-factor tables, the
+// most z segments, its tile shapes (segments of 64 x columns by rows, one
+// wavefront each), and the shares of a value that the truncated look-ahead may
+// miss (FP64, FP32 storage).
+constexpr int kStreamDepths = 4;
+constexpr int kStreamDepth[kStreamDepths] = {16, 28, 44, 60};
+constexpr int kStreamBlock = 8;
+constexpr int kStreamRowPad = 16;
+constexpr int kStreamPad = 80;
+constexpr int kStreamMaxSeg = 16;
+struct StreamShape {
+  int segs, rows;
+};
+constexpr int kStreamShapes = 4;
+constexpr StreamShape kStreamShape[kStreamShapes] = {{4, 4}, {3, 4}, {2, 4}, {1, 4}};
+constexpr double kTruncate64 = 7e-18;
+constexpr double kTruncate32 = 1e-14;
+
+// One walk position's factors of the streaming step (the walk goes up or down,
+// position s is level s or nz-1-s): the elimination e_s = em (r_s + tkb) + ea
+// e_{s-1} and the z advection.  Forward FP64: c0 and c2 are the signed 1/hz of
+// the face ahead and of the face behind (0: a wall), so that c0 w (theta +
+// theta) and c2 w (theta + theta) add up to the net flux.  Forward FP32: c0 and
+// c2 are 1 where those faces are interior faces, else 0, and c1 is 1/hz.
+// Reverse: the face ahead gives w (c0 mu_{s+1} - c1 mu_s), the one behind
+// w (c2 mu_s - c3 mu_{s-1}).
+template <typename T>
+struct alignas(64) StreamRow {
+  double em, ea, tkb, unused;
+  T c0, c1, c2, c3;
+};
+// Whether a look-ahead's elimination values (two registers a level) fit beside
+// the rest in a workgroup of that many wavefronts: 16 get 128 registers each,
+// 12 get 168, 8 and fewer 256.
+constexpr bool stream_fits(int levels, int waves) {
+  return levels <= 28 || (levels <= 44 && waves <= 12) || waves <= 8;
+}
+
+// A context's cut into tiles and segments; per walk direction and segment:
+// first position, end, walk start, walk end.
+struct StreamPlan {
+  int shape = 0, nseg = 1;
+  std::vector<int> seg[2];
+};
+// before[d][s] / after[d][s]: how far before / after position s of walk
+// direction d (0 up, 1 down) values still matter to the solution at s.
+StreamPlan stream_plan(int nx, int ny, int nz, bool f64, int cus, int depth, const std::vector<int> (&before)[2],
+                       const std::vector<int> (&after)[2]);
+template <typename T>
+struct StreamSys {
+  const StreamRow<T>* row;   // from position -kStreamRowPad to nz + kStreamRowPad (zero outside 0 .. nz-1)
+  const double* cb;          // back substitution, from -kStreamPad to nz + kStreamPad (zero outside)
+};
+
 }  // namespace mr
 
 struct mr_ctx {
@@ -127,6 +183,13 @@ struct mr_ctx {
   mr::SweepSys sw[mr::NKINDS];     // column-sweep factors per step kind
   mr::SweepSys swt[mr::NKINDS];    // the same for the transposed systems (reverse steps)
   mr::SweepSys swid;               // identity factors (the start-up step's reverse: no solve)
+  // streaming-step factors: [transposed][walking down][step kind] (of the context's precision)
+  mr::StreamSys<double> sr64[2][2][mr::NKINDS];
+  mr::StreamSys<float> sr32[2][2][mr::NKINDS];
+  int stream_d;                    // look-ahead of the streaming step: 1 + index into kStreamDepth (0: it does not apply)
+  int stream_shape;                // its tile shape (index into kStreamShape)
+  int stream_nseg;                 // z segments per column
+  const int* stream_seg[2];        // per walk direction and segment: first position, end, walk start, walk end
   int sweep_shape;                 // column-sweep tile shape (index into kSweepShape)
   int sweep_pref;                  // run step sequences as column sweeps
   int sweep_single;                // run single steps as a column sweep and its back substitution
@@ -188,6 +251,13 @@ hipError_t launch_sweep_bwd_steps(mr_ctx* c, int64_t n0, int count, const void* 
 hipError_t launch_sweep_bwd0(mr_ctx* c, const void* mu_next, const void* mu_cur, void* out, const void* u,
                              const void* v, const void* w, hipStream_t s);
 hipError_t launch_sweep_seed(mr_ctx* c, int64_t n, const void* lam, void* out, hipStream_t s);
+// The streaming step (one kernel; contexts with stream_d > 0): theta^{n+1},
+// and the reverse step n >= 1 without lam_add.  q: the step's index in its
+// sequence where the context would run column sweeps instead, else -1.
+hipError_t launch_stream_step(mr_ctx* c, int64_t n, int q, const void* thp, const void* thc, void* out,
+                              const void* u, const void* v, const void* w, hipStream_t s);
+hipError_t launch_stream_step_backward(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* out,
+                                       const void* u, const void* v, const void* w, hipStream_t s);
 // Grows the context's reduction scratch to at least `bytes`.
 hipError_t ensure_red(mr_ctx* c, size_t bytes);
 // The fixed device memory of the allocation-free Nusselt entry point: looks up
