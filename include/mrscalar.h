@@ -291,7 +291,7 @@ int mr_nusselt(mr_ctx* ctx, const void* theta, const void* w, double* dev_profil
 /* mr_nusselt for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same kernels and results (bit for bit) as mr_nusselt with host_out NULL, with
- * the reduction partials in a fixed device array of the library (3.15 MB per
+ * the reduction partials in a fixed device array of the library (2.1 MB per
  * GPU, set up by mr_init on its device and held until the process ends)
  * instead of the context's lazily allocated buffer.  Allocates nothing.
  * Limit: nz <= 1024 (MR_ESHAPE beyond).  Every call on one GPU shares that

@@ -810,7 +810,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   }
   const size_t o_seg[2] = {pk.put(plan.seg[0]), pk.put(plan.seg[1])};
   vector<double> dcz(P.z.dc);
-  size_t o_hx64 = pk.put(P.x.h), o_hy64 = pk.put(P.y.h), o_dcz = pk.put(dcz), o_hz64 = pk.put(P.z.h);
+  size_t o_hx64 = pk.put(P.x.h), o_hy64 = pk.put(P.y.h), o_dcz = pk.put(dcz), o_idcz = pk.put(inv(dcz)), o_hz64 = pk.put(P.z.h);
 
   mr_ctx* c = new (std::nothrow) mr_ctx();
   if (!c) return MR_ENOMEM;
@@ -842,6 +842,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
         s = t;
       }
     c->atot = s + comp;
+    c->atot_lo = (s - c->atot) + comp;
     c->vtot = c->atot * (P.z.f[P.z.n] - P.z.f[0]);
   }
   hipError_t e = hipGetDevice(&c->device);
@@ -895,6 +896,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   c->hx64 = (const double*)(base + o_hx64);
   c->areaw = (const double*)(base + o_hy64);
   c->dcz = (const double*)(base + o_dcz);
+  c->idcz = (const double*)(base + o_idcz);
   c->hz64 = (const double*)(base + o_hz64);
   *out = c;
   return MR_OK;

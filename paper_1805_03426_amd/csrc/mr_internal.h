@@ -172,7 +172,7 @@ struct mr_ctx {
   int last_err;
   int L, nch;                      // z chunk length and count of the line solver (0: columns too
                                    // tall for it; only the column-sweep step runs)
-  double atot;                     // total horizontal area
+  double atot, atot_lo;            // total horizontal area (sum of the cells' rounded areas), its rounding error
   double vtot;                     // domain volume (atot times the height)
   double tau[mr::NKINDS];
   void* tables;                    // one device block with every table
@@ -197,6 +197,7 @@ struct mr_ctx {
   const double* areaw;             // [ny] hy_j (area = hx_i * hy_j, built in kernel)
   const double* hx64;              // [nx]
   const double* dcz;               // [nz+1] centre distances across z faces (wall: half cell)
+  const double* idcz;              // [nz+1] 1/dcz
   const double* hz64;              // [nz]
   void* interp_tmp;                // forward refinement intermediates (lazy)
   size_t interp_tmp_bytes;
@@ -290,6 +291,19 @@ __device__ __forceinline__ DD wave_sum(DD v) {
     v = dd_merge(v, o);
   }
   return v;
+}
+
+// V consecutive values from p (one load; p needs its element's alignment only).
+template <typename T, int V>
+__device__ __forceinline__ void load_vec(const T* p, T* o) {
+  if constexpr (V == 1) {
+    o[0] = *p;
+  } else {
+    typedef T vt __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+    const vt x = *reinterpret_cast<const vt*>(p);
+#pragma unroll
+    for (int q = 0; q < V; ++q) o[q] = x[q];
+  }
 }
 
 // Step-type bookkeeping shared by the host API and the launchers.
