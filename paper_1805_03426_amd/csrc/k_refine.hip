@@ -812,8 +812,9 @@ __global__ void __launch_bounds__(256) ty_fused(RefArgs<T> A, int nrowc) {
     if (Jo >= J0 && Jo < J1) emit(Jo);
     cur = nxt;
   }
-  // rows whose later sources lie beyond a wall
-  for (int Jo = max(J0, Jb - 2); Jo < J1; ++Jo) {
+  // rows whose later sources lie beyond a wall (the window shifts once per row
+  // from the last one loaded, also where the range holds a single row)
+  for (int Jo = Jb - 2; Jo < J1; ++Jo) {
 #pragma unroll
     for (int d = 0; d < 4; ++d)
 #pragma unroll
@@ -823,7 +824,7 @@ __global__ void __launch_bounds__(256) ty_fused(RefArgs<T> A, int nrowc) {
       }
 #pragma unroll
     for (int q = 0; q < MY; ++q) wu[4][q] = ww[4][q] = T(0);
-    emit(Jo);
+    if (Jo >= J0) emit(Jo);
   }
 }
 
@@ -931,11 +932,12 @@ __global__ void __launch_bounds__(256) tz_fused(RefArgs<T> A, int nlayc) {
     const int Ko = K - 2;
     if (Ko >= K0 && Ko < K1) emit(Ko);
   }
-  for (int Ko = max(K0, Kb - 2); Ko < K1; ++Ko) {
+  // layers whose later sources lie beyond the top wall, as in ty_fused
+  for (int Ko = Kb - 2; Ko < K1; ++Ko) {
     shift();
 #pragma unroll
     for (int p = 0; p < MZ; ++p) wu[4][p] = wv[4][p] = T(0);
-    emit(Ko);
+    if (Ko >= K0) emit(Ko);
   }
 }
 
