@@ -24,6 +24,8 @@
 
 #include <string.h>
 
+#include <type_traits>
+
 #include "mr_internal.h"
 
 namespace mr {
@@ -576,7 +578,10 @@ void launch_eo(bool expz, bool ord4, dim3 grid, dim3 block, hipStream_t s, const
 // chunks) a wavefront gets at most 128 VGPRs, and the variants (side walls,
 // explicit z share, fourth-order faces, stretched x or y) spill there; columns
 // of at most 8 chunks launch them compiled for 512 threads (up to 256 VGPRs,
-// no spill).  The plain uniform-width kernels fit either way and stay at 1024.
+// no spill), columns of 9 to 12 for 768 (up to 168: at 150 x 150 x 300 in FP64
+// the reverse step with walls, fourth order and explicit z takes 190 us instead
+// of 453, the forward one 152 instead of 180).  The plain uniform-width kernels
+// fit either way and stay at 1024.
 template <typename T, int LL, int MODE, int R, int MB, int PF, int MT>
 void launch_variant(bool walls, bool expz, bool ord4, bool uxy, dim3 grid, dim3 block, hipStream_t s,
                     const LineArgs<T>& a) {
@@ -586,9 +591,9 @@ void launch_variant(bool walls, bool expz, bool ord4, bool uxy, dim3 grid, dim3 
     if (walls) launch_eo<T, LL, MODE, R, MB, PF, true, MT>(expz, ord4, grid, block, s, a);
     else if (uxy && !expz && !ord4) {
       // the plain FP32 step runs two levels of loads ahead (forward with chunks
-      // of up to 36 levels: 1-3% faster; reverse with chunks of 32: 1%); those
+      // of up to 36 levels: 1-3% faster; reverse with chunks of up to 32: 1%); those
       // kernels do not spill at that depth, the other variants do
-      constexpr int PFU = (sizeof(T) == 4 && ((MODE == FWD && LL <= 36) || (MODE == BWD && LL == 32))) ? 2 : PF;
+      constexpr int PFU = (sizeof(T) == 4 && ((MODE == FWD && LL <= 36) || (MODE == BWD && LL <= 32))) ? 2 : PF;
       launch_one<T, LL, MODE, R, MB, PFU, false, false, false, true>(grid, block, s, a);
     }
     else launch_eo<T, LL, MODE, R, MB, PF, false, MT>(expz, ord4, grid, block, s, a);
@@ -651,12 +656,24 @@ hipError_t launch_line(mr_ctx* c, LineArgs<T> a, hipStream_t s) {
     if (uxy && !walls && !expz && !ord4 && c->nch > 8 && wide64_ok<MODE>(c->L))
       return launch_line_wide64<T, MODE>(c, a, s);
   }
+  const auto run = [&](auto len) {
+    constexpr int LL = decltype(len)::value;
+    if (c->nch <= 8) return launch_variant<T, LL, MODE, rows, mb, pf, 512>(walls, expz, ord4, uxy, grid, block, s, a);
+    if constexpr (LL >= 32) {   // shorter chunks come at most 8 to a column
+      if constexpr (LL == 32)
+        if (c->nch <= 12) return launch_variant<T, LL, MODE, rows, mb, pf, 768>(walls, expz, ord4, uxy, grid, block, s, a);
+      launch_variant<T, LL, MODE, rows, mb, pf, 1024>(walls, expz, ord4, uxy, grid, block, s, a);
+    }
+  };
+  if (c->nch > 8 && c->L < 32) return hipErrorInvalidValue;
   switch (c->L) {
-#define MR_CASE(LL)                                                                             \
-  case LL:                                                                                      \
-    if (c->nch <= 8) launch_variant<T, LL, MODE, rows, mb, pf, 512>(walls, expz, ord4, uxy, grid, block, s, a); \
-    else launch_variant<T, LL, MODE, rows, mb, pf, 1024>(walls, expz, ord4, uxy, grid, block, s, a); \
+#define MR_CASE(LL)                             \
+  case LL:                                      \
+    run(std::integral_constant<int, LL>());     \
     break;
+    MR_CASE(8)
+    MR_CASE(16)
+    MR_CASE(24)
     MR_CASE(32)
     MR_CASE(36)
     MR_CASE(40)

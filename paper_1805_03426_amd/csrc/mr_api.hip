@@ -253,7 +253,7 @@ int check_desc(const mr_desc* d, Problem& P) {
                uniform_axis(P.y) && d->z_explicit == 0.0 && d->face_order != 4;
   if (d->step_method == 2 && !P.sweep_ok) return MR_EINVAL;
   // columns beyond the line solver's chunks need the sweeps
-  if (nz > (int64_t)mr::kMaxChunks * mr::kChunkLens[2] && (!P.sweep_ok || d->step_method == 1))
+  if (nz > (int64_t)mr::kMaxChunks * mr::kMaxChunkLen && (!P.sweep_ok || d->step_method == 1))
     return MR_ESHAPE;
   return MR_OK;
 }
@@ -434,17 +434,32 @@ vector<double> stream_cb(const StreamHost& w) {
   return cb;
 }
 
-// Shortest chunk length that splits nz levels into at most
-// kMaxChunks chunks.
-int choose_chunks(int nz, int& L, int& nch) {
-  for (int l : mr::kChunkLens) {
-    if ((nz + l - 1) / l <= mr::kMaxChunks) {
-      L = l;
-      nch = (nz + l - 1) / l;
-      return MR_OK;
-    }
-  }
-  return MR_ESHAPE;
+// Chunk length and count of the line solver for `tiles` column tiles (one
+// workgroup each) of nz levels.  A chunk is one wavefront's serial walk, so
+// short chunks shorten the step until the registers of a CU run out (about 8
+// wavefronts).  One round of tiles: the shortest chunks that make at most 8.
+// Several rounds: at most 4, so that two workgroups share a CU; columns too
+// tall for that, chunks of 24 if they make at most 8 (with 32 a workgroup of 5
+// or 6 wavefronts leaves the rest of its CU idle).  Taller ones: the shortest
+// of 32, 36 and 40 that makes at most 16.  The plain FP64 step in several rounds
+// takes chunks of 24 from 161 levels on only (150^3 61 us with 32, 63 with 24;
+// 300 x 280 x 90 108 and 123).  One step in us, against chunks of 32:
+// 64^3 13.3 to 28.0 (FP64), 9.3 to 17.6 (FP32); 128^3 26 to 35, 15.8 to 19.5;
+// 160 x 160 x 64 24.4 to 35.4, 15.2 to 20.5; 251 x 251 x 192 168 to 204, 86 to
+// 106; side walls, fourth-order faces and an explicit z share at 186^3 134 to
+// 160, 78 to 101; the same at 251 x 251 x 128 with chunks of 16 (8 of them)
+// instead of 32 (4): 133 to 122.
+int choose_chunks(int nz, int64_t tiles, int cus, bool plain64, int& L, int& nch) {
+  const int most = tiles <= cus ? 8 : 4;
+  L = 0;
+  for (int l : mr::kChunkLens)
+    if (!L && l <= 32 && l * most >= nz && (l != 24 || most == 8 || !plain64)) L = l;
+  if (!L && 24 * 8 >= nz && (!plain64 || nz > 160)) L = 24;
+  for (int l : mr::kChunkLens)
+    if (!L && l >= 32 && l * mr::kMaxChunks >= nz) L = l;
+  if (!L) return MR_ESHAPE;
+  nch = (nz + L - 1) / L;
+  return MR_OK;
 }
 
 // Byte buffer that hands out 256-byte aligned slots.
@@ -716,7 +731,13 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   int L = 0, nch = 0;
   // columns taller than the line solver's chunks: only the column-sweep step
   // (check_desc has made sure that it applies)
-  if (choose_chunks(P.z.n, L, nch) != MR_OK) L = nch = 0;
+  int cus = 0, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    cus = 256;
+  const int lrows = desc->precision == MR_FP64 ? 2 : 1, lcols = mr::kWave / lrows;   // patch of a line workgroup
+  const int64_t ltiles = (int64_t)((P.x.n + lcols - 1) / lcols) * ((P.y.n + lrows - 1) / lrows);
+  if (choose_chunks(P.z.n, ltiles, cus, desc->precision == MR_FP64 && P.sweep_ok, L, nch) != MR_OK) L = nch = 0;
   const int npad = std::max(nch * L, P.z.n);
 
   vector<double> R[3];
@@ -733,13 +754,24 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   double taus[mr::NKINDS];
   const int nz = P.z.n;
   const bool f64 = desc->precision == MR_FP64;
+  // the streaming step runs wherever it applies but on small grids where the
+  // line solver is faster: FP64 with copies into LDS of 4 bytes (odd N_x): 127^3
+  // 54 us against 30, 175^3 86 against 99; FP64 columns of at most 64 levels in
+  // one round of tiles: 64^3 14.8 us against 13.3, 128 x 128 x 64 19.7 against
+  // 16.1 (but 128^3 27.0 against 26.2, 160 x 160 x 64 21.5 against 24.4, 60 x 60
+  // x 128 18.4 against 24.4); FP32: 128^3 24 us against 16, 160^3 36 against 31,
+  // 176^3 41 against 51
+  const bool one_round = ltiles <= cus;
+  const bool streams = P.sweep_ok && desc->step_method == 0 &&
+                       (nch == 0 || (int64_t)P.x.n * P.y.n * nz >= 4500000 ||
+                        (f64 && P.x.n % 2 == 0 && !(one_round && nz <= 64)));
   size_t sro[2][2][mr::NKINDS], scbo[2][2][mr::NKINDS];   // streaming tables: [transposed][down][kind]
   const double eps = f64 ? mr::kTruncate64 : mr::kTruncate32;
   int ahead = 0;                                      // the streaming step's look-ahead
   vector<int> after[2], before[2];                    // its reach after / before each walk position
   for (int d = 0; d < 2; ++d) after[d].assign(nz, 0), before[d].assign(nz, 0);
   auto pack_stream = [&](const SweepHost& h, int kind, bool rev) {
-    if (!P.sweep_ok || desc->step_method != 0) return;
+    if (!streams) return;
     for (int d = 0; d < 2; ++d) {
       const StreamHost w = stream_walk(h, d);
       sro[rev][d][kind] = f64 ? pk.put(stream_rows<double>(P.z, h, w, rev, d)) : pk.put(stream_rows<float>(P.z, h, w, rev, d));
@@ -791,19 +823,10 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   shid.up_cb.assign(nz, 0.0); shid.dn_cb.assign(nz, 0.0);
   shid.tkb.assign(nz, 0.0);
   const SweepOffsets swido = pack_sweep(pk, shid);
-  // the streaming step's look-ahead, tiles and z segments.  It runs wherever it
-  // applies but on small grids whose copies into LDS are of 4 bytes (FP64, odd
-  // N_x) and on small FP32 grids, where the line solver is faster: FP64 127^3
-  // 38 us against 54, 175^3 105 against 86; FP32 128^3 19.5 us against 24, 160^3
-  // 31 against 36, 176^3 53 against 41, 175^3 58 against 52
-  const bool streams = nch == 0 || (f64 && P.x.n % 2 == 0) || (int64_t)P.x.n * P.y.n * nz >= 4500000;
-  int cus = 0, dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
+  // the streaming step's look-ahead, tiles and z segments
   int stream_d = 0;
   mr::StreamPlan plan;
-  if (P.sweep_ok && desc->step_method == 0 && streams) {
+  if (streams) {
     for (int d = mr::kStreamDepths; d > 0; --d)
       if (ahead <= mr::kStreamDepth[d - 1]) stream_d = d;
     if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, cus, stream_d - 1, before, after);
