@@ -693,7 +693,20 @@ bool launch_tx_row(mr_ctx* c, const RefArgs<T>& a, hipStream_t s) {
 // whose R^T sources are complete (R_y stencils reach two rows at a wall), as
 // ty_split does.  The per-row R_y entries are wave-uniform (scalar loads);
 // the loads of a row are issued one row ahead of its use (13-17% faster).
-constexpr int kYRows = 32;   // coarse rows per thread (plus two halo rows each side)
+// A thread walks its rows one after the other, two halo rows each side on top,
+// so fewer rows per thread shorten the kernel while wavefronts are few: below
+// 10 wavefronts a CU with 32 rows each, as few rows as make 16 a CU.  In us, 32
+// rows against the rule: 40 x 27 coarse (50 levels, M_y = 3, FP64) 53 to 9;
+// 32 x 32 (64 levels, FP32) 56 to 8; 128 x 128 (256 levels) 83 to 61 in FP32, 110
+// to 98 in FP64; 120 x 134 (300 levels, M_y = 3, FP64), 12 a CU, 121 (16 rows: 128).
+constexpr int kYRows = 32;
+inline int rows_per_thread(int n, int most, int64_t wavefronts_per_range) {
+  const int64_t cus = 256, ranges = (n + most - 1) / most;
+  int64_t want = ranges;
+  if (wavefronts_per_range * ranges < 10 * cus) want = (16 * cus + wavefronts_per_range - 1) / wavefronts_per_range;
+  want = std::min<int64_t>(std::max(want, ranges), n);
+  return (int)((n + want - 1) / want);
+}
 
 template <typename T, int MY>
 __global__ void __launch_bounds__(256) ty_fused(RefArgs<T> A, int nrowc) {
@@ -834,7 +847,9 @@ __global__ void __launch_bounds__(256) ty_fused(RefArgs<T> A, int nrowc) {
 // does, writes gW, keeps the adjoints of the last five layers, and gathers
 // every layer whose R_z^T sources are complete (R_z stencils reach two layers
 // at a wall), as tz_split does.  The per-layer R_z entries are wave-uniform.
-constexpr int kZLayers = 16;   // coarse layers per thread (plus two halo layers each side)
+// Layers per thread as the rows of ty_fused: 40 x 27 x 25 coarse (FP64) 20 us to
+// 6; 32^3 (FP32) 22 to 5; 128^3 29 to 24 (FP32), 47 to 37 (FP64).
+constexpr int kZLayers = 16;
 
 template <typename T, int MZ>
 __global__ void __launch_bounds__(256) tz_fused(RefArgs<T> A, int nlayc) {
@@ -1226,9 +1241,8 @@ hipError_t refine_transpose_t(mr_ctx* c, const Geom<T>& g, const void* gu, const
   if (c->my <= 4) {
     a.in0 = gUzy; a.in1 = gVzy; a.in2 = gWzy;
     a.out0 = gUz; a.out2 = gWz; a.out3 = gVz;
-    const int nrc = (c->ncy + kYRows - 1) / kYRows;
-    const int nrowc = (c->ncy + nrc - 1) / nrc;
     const int ntx = (c->ncx + kWave - 1) / kWave;
+    const int nrowc = rows_per_thread(c->ncy, kYRows, (int64_t)ntx * (c->nz + 1));
     const dim3 grid((unsigned)((int64_t)ntx * (c->nz + 1) * ((c->ncy + nrowc - 1) / nrowc))), block(kWave);
     switch (c->my) {
       case 1: hipLaunchKernelGGL((ty_fused<T, 1>), grid, block, 0, s, a, nrowc); break;
@@ -1250,9 +1264,8 @@ hipError_t refine_transpose_t(mr_ctx* c, const Geom<T>& g, const void* gu, const
   if (c->mz <= 4) {
     a.in0 = gUz; a.in1 = gVz; a.in2 = gWz;
     a.out0 = (T*)gU; a.out1 = (T*)gV; a.out2 = (T*)gW;
-    const int nlc = (c->ncz + kZLayers - 1) / kZLayers;
-    const int nlayc = (c->ncz + nlc - 1) / nlc;
     const int ntx = (c->ncx + kWave - 1) / kWave, nty = (c->ncy + 3) / 4;
+    const int nlayc = rows_per_thread(c->ncz, kZLayers, (int64_t)ntx * nty * 4);
     const dim3 grid((unsigned)((int64_t)ntx * nty * ((c->ncz + nlayc - 1) / nlayc))), block(256);
     switch (c->mz) {
       case 1: hipLaunchKernelGGL((tz_fused<T, 1>), grid, block, 0, s, a, nlayc); break;
