@@ -18,6 +18,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mr_internal.h"
 
@@ -171,18 +172,29 @@ __global__ void __launch_bounds__(256) stage_x(RefArgs<T> A) {
 //   Y: for the layer's dense levels, the tile's rows and halo columns
 //      I0-1 .. I0+TI, split the z-refined U, W along y and march V (as
 //      stage_y), into LDS;
-//   X: for the tile's dense cells, split V, W along x; each lane runs the x
-//      march of U up to its own sub-column (the same operations in the same
-//      order as stage_x).
+//   X: for the tile's dense cells, split V, W along x and march U (the same
+//      operations in the same order as stage_x), one lane per coarse cell and
+//      dense row for M_x up to 4, which stores its sub-columns together.
 // Each dense value is written once, 64 consecutive columns per row; the only
-// HBM reads are the coarse levels (cache-resident halo re-reads).  On a
+// HBM reads are the coarse levels (cache-resident halo re-reads).  The tiles of
+// one layer range are dealt to the XCDs in contiguous runs, so that one L2 holds
+// the halo of neighbouring tiles.  Bound by latency and LDS between its two
+// barriers a layer (three workgroups a CU in FP64); with one lane per dense
+// column and divisions per item the vector units were busy 70-80% of the time
+// (188 instructions per dense cell in FP32, 90 now).  In us, before and now (what
+// a fill of the outputs takes): 64^3 FP64 25 and 12; 256^3 FP64 134 and 96 (63),
+// FP32 100 and 69; 576^3 FP32 936 and 783 (333); 480 x 402 x 300 (M = 4, 3, 2)
+// FP64 382 and 294 (205); 300^3 (M = 3) 269 and 200; 200^3 (M = 1) 467 and 207.  On a
 // periodic axis the halo wraps and the stencil of cell I is I-1 .. I+1; on a
 // walled axis the stencil is the one-sided one of the R tables next to the
 // walls (every stencil cell of the tile then lies in the halo as long as a
 // tile holds at least two cells along that axis, which the launcher ensures),
 // the wall faces are taken as zero, and halo cells beyond a wall are computed
 // but never read.
+// dense columns of a tile's rows (M_x = 1: 32, since 64 coarse columns and their
+// halo leave a workgroup one row of them)
 constexpr int kFuseCols = 64;
+__host__ __device__ constexpr int fuse_cols(int mx) { return mx == 1 ? kFuseCols / 2 : kFuseCols; }
 
 __device__ __forceinline__ int wrapm(int i, int n) {
   i %= n;
@@ -235,18 +247,43 @@ __device__ __forceinline__ T rdot3(const T* R, const T q[3]) {
   return R[0] * q[0] + R[1] * q[1] + R[2] * q[2];
 }
 
-// LDS element counts of refine_fused (tables first, then the stage fields).
+// LDS element counts of refine_fused (tables first, then the stage fields,
+// whose rows hold the halo columns of the widest tile).
+__host__ __device__ inline int fused_stride(int mx) { return fuse_cols(mx) / mx + 3; }
 __host__ __device__ inline int fused_tables(int TI, int TJ, int mx, int my) {
-  const int NXH = TI + 3, RY = TJ * my, CX = TI * mx;
-  return NXH + 5 * RY + 4 * CX + 2 * kZTab;
+  const int RY = TJ * my, CX = TI * mx;
+  return fused_stride(mx) + 5 * RY + 4 * CX + 2 * kZTab;
 }
-__host__ __device__ inline int fused_fields(int TI, int TJ, int my, int mz) {
-  const int NXH = TI + 3, NYH = TJ + 2, RY = TJ * my;
-  return 2 * mz * NYH * NXH + (mz + 1) * NYH * NXH + mz * RY * NXH + (mz + 1) * RY * NXH +
-         mz * TJ * (my + 1) * NXH;
+__host__ __device__ inline int fused_fields(int TJ, int mx, int my, int mz) {
+  const int NXS = fused_stride(mx), NYH = TJ + 2, RY = TJ * my;
+  return 2 * mz * NYH * NXS + (mz + 1) * NYH * NXS + mz * RY * NXS + (mz + 1) * RY * NXS +
+         mz * TJ * (my + 1) * NXS;
 }
 
-template <typename T, bool NT>
+// N consecutive values, stored at any element alignment as wide as N allows
+// (three as two and one: a three-wide vector store writes four).
+template <typename T, int N>
+struct Pack {
+  T v[N];
+};
+template <bool NT, typename T, int N>
+__device__ __forceinline__ void store_pack(T* p, const Pack<T, N>& a) {
+  if constexpr (N == 2 || N == 4) {
+    typedef T vec __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+    vec x;
+#pragma unroll
+    for (int q = 0; q < N; ++q) x[q] = a.v[q];
+    if constexpr (NT) __builtin_nontemporal_store(x, (vec*)p);
+    else *(vec*)p = x;
+  } else {
+    static_assert(N == 1 || N == 3, "one to four values");
+    if constexpr (N == 3) store_pack<NT>(p, Pack<T, 2>{a.v[0], a.v[1]});
+    if constexpr (NT) __builtin_nontemporal_store(a.v[N - 1], p + N - 1);
+    else p[N - 1] = a.v[N - 1];
+  }
+}
+
+template <typename T, int MX, bool NT>
 __global__ void __launch_bounds__(256) refine_fused(RefArgs<T> A, int TI, int TJ, int nbx, int nby,
                                                     int KC) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -255,23 +292,25 @@ __global__ void __launch_bounds__(256) refine_fused(RefArgs<T> A, int TI, int TJ
   const int nx = A.nx, nz = A.nz;
   const int nxy = nx * A.ny;
   const int NXH = TI + 3, NYH = TJ + 2, RY = TJ * my, CX = TI * mx;
+  const int NXS = fused_stride(MX > 0 ? MX : mx);   // LDS row stride
   // per-workgroup tables
-  T* const tIHX = sm;                          // [NXH] 1/HX of the halo columns
-  T* const tRy = tIHX + NXH;                   // [RY][3]
+  T* const tIHX = sm;                          // [NXS] 1/HX of the halo columns
+  T* const tRy = tIHX + NXS;                   // [RY][3]
   T* const tHy = tRy + 3 * RY;                 // [RY]
   T* const tIhy = tHy + RY;                    // [RY]
   T* const tRx = tIhy + RY;                    // [CX][3]
   T* const tHx = tRx + 3 * CX;                 // [CX]
   T* const tZ = tHx + CX;                      // [2][kZTab] per-layer z tables, by layer parity
   // stage fields
-  T* const Uz = tZ + 2 * kZTab;                // [mz][NYH][NXH]
-  T* const Vz = Uz + mz * NYH * NXH;           // [mz][NYH][NXH]
-  T* const Wz = Vz + mz * NYH * NXH;           // [mz+1][NYH][NXH]
-  T* const Uzy = Wz + (mz + 1) * NYH * NXH;    // [mz][RY][NXH]
-  T* const Wzy = Uzy + mz * RY * NXH;          // [mz+1][RY][NXH]
-  T* const Vzy = Wzy + (mz + 1) * RY * NXH;    // [mz][TJ][my+1][NXH]
-  const int b = blockIdx.x;
-  const int bx = b % nbx, by = (b / nbx) % nby, kc = b / (nbx * nby);
+  T* const Uz = tZ + 2 * kZTab;                // [mz][NYH][NXS]
+  T* const Vz = Uz + mz * NYH * NXS;           // [mz][NYH][NXS]
+  T* const Wz = Vz + mz * NYH * NXS;           // [mz+1][NYH][NXS]
+  T* const Uzy = Wz + (mz + 1) * NYH * NXS;    // [mz][RY][NXS]
+  T* const Wzy = Uzy + mz * RY * NXS;          // [mz+1][RY][NXS]
+  T* const Vzy = Wzy + (mz + 1) * RY * NXS;    // [mz][TJ][my+1][NXS]
+  const int tiles = nbx * nby, kc = blockIdx.x / tiles;
+  const int b = xcd_remap(blockIdx.x - kc * tiles, tiles);
+  const int bx = b % nbx, by = b / nbx;
   const int I0 = bx * TI, J0 = by * TJ;
   const int TJv = min(TJ, ncy - J0);           // rows of this tile
   const int K0 = kc * KC, K1 = min(ncz, K0 + KC);
@@ -301,10 +340,20 @@ __global__ void __launch_bounds__(256) refine_fused(RefArgs<T> A, int TI, int TJ
   const bool zu0 = A.wx && (fI <= 0 || fI >= ncx), zu1 = A.wx && (fI + 1 <= 0 || fI + 1 >= ncx);
   const bool zv0 = A.wy && (fJ <= 0 || fJ >= ncy), zv1 = A.wy && (fJ + 1 <= 0 || fJ + 1 >= ncy);
   const T ziHX = g.iHX[zI], ziHY = g.iHY[zJ];
-  // stage-x lane roles: column col of the tile, sub-column sub of coarse column Ix
-  const int col = t % kFuseCols, grp = t / kFuseCols;
-  const int Ix = I0 + col / mx, sub = col - (col / mx) * mx;
-  const bool xon = col < CX && Ix < ncx;
+  // stage-y item of this thread: halo column yl of the items yg, yg + yn, ...
+  const int yn = 256 / (NXH - 1), yg = t / (NXH - 1), yl = t - yg * (NXH - 1);
+  const bool yon = yg < yn;
+  // stage-x roles.  MX > 0: PC sub-columns from sub on of coarse column Ix
+  // (PC = MX but where MX values exceed the 16 bytes of one store, whose halves
+  // would leave every line half written: two lanes then), in the dense rows xg,
+  // xg + xn, ... of the tile, one row per item; otherwise dense column col,
+  // sub-column sub of Ix.
+  constexpr int PC = MX > 0 ? (MX * sizeof(T) == 32 ? MX / 2 : MX) : 1;
+  const int xlanes = MX > 0 ? TI * (MX / PC) : kFuseCols;   // lanes of a dense row
+  const int xn = 256 / xlanes, xg = t / xlanes;
+  const int col = (t - xg * xlanes) * PC, xc = col / (MX > 0 ? MX : mx);
+  const int Ix = I0 + xc, sub = col - xc * mx;
+  const bool xon = xg < xn && col < CX && Ix < ncx;
   // (M_x = 1: R = [0 1 0] on the centred stencil, whose table entries wrap
   // even on a walled axis; the halo column of the cell itself is Ix - I0 + 1)
   int xloc[3];
@@ -312,14 +361,15 @@ __global__ void __launch_bounds__(256) refine_fused(RefArgs<T> A, int TI, int TJ
     const int p = !xon ? 0 : (mx == 1 ? Ix - I0 + r : g.sx[Ix * 3 + r] - (I0 - 1));
     xloc[r] = A.wx ? p : wrapm(p, ncx);
   }
+  // row / my of a tile row as a product: exact for up to 6 my rows and my up to 64
+  const unsigned imy = 65536u / my + 1;
 
-  ZLoad<T> cur, nxt;
+  ZLoad<T> cur;
   if (zon && K0 < K1) z_load<T>(A, K0, zI, zIp, zJ, zJp, cur);
   if (K0 < K1) ztab_store(tZ + (K0 & 1) * kZTab, mz, t, ztab_load(g, K0, mz, t));
   __syncthreads();   // tables
   for (int K = K0; K < K1; ++K) {
-    // the next layer's coarse values and z tables, in flight while this one is refined
-    if (zon && K + 1 < K1) z_load<T>(A, K + 1, zI, zIp, zJ, zJp, nxt);
+    // the next layer's z tables, in flight while this one is refined
     const T tnext = K + 1 < K1 ? ztab_load(g, K + 1, mz, t) : T(0);
     const T* const zt = tZ + (K & 1) * kZTab;
     const T* const ihzK = zt + 4 * kFuseMaxMz;
@@ -336,43 +386,53 @@ __global__ void __launch_bounds__(256) refine_fused(RefArgs<T> A, int TI, int TJ
       for (int m = 0; m < mz; ++m) {
         const T* R = zt + 3 * m;
         const T a = rdot3(R, u0), bb = rdot3(R, u1), c = rdot3(R, v0), d = rdot3(R, v1);
-        Uz[(m * NYH + zr) * NXH + zl] = a;
-        Vz[(m * NYH + zr) * NXH + zl] = c;
-        Wz[(m * NYH + zr) * NXH + zl] = wv;
+        Uz[(m * NYH + zr) * NXS + zl] = a;
+        Vz[(m * NYH + zr) * NXS + zl] = c;
+        Wz[(m * NYH + zr) * NXS + zl] = wv;
         if (m < mz - 1) wv = wv - zt[3 * kFuseMaxMz + m] * ((bb - a) * ziHX + (d - c) * ziHY);
       }
-      Wz[(mz * NYH + zr) * NXH + zl] = cur.wt;
+      Wz[(mz * NYH + zr) * NXS + zl] = cur.wt;
+      // the next layer's coarse values, in flight during stages y and x
+      if (K + 1 < K1) z_load<T>(A, K + 1, zI, zIp, zJ, zJp, cur);
     }
     __syncthreads();
-    // ---- Y: items (tile row jt, level m, halo column l)
-    const int ny_items = TJv * mz * (NXH - 1);
-    for (int it = t; it < ny_items; it += blockDim.x) {
-      const int l = it % (NXH - 1), rest = it / (NXH - 1);
-      const int m = rest % mz, jt = rest / mz;
-      T u0[3], u1[3], w0[3], w1[3];
-      // first stencil row of tile row jt (centred unless next to a y wall)
-      // (M_y = 1: the centred rows, as for M_x = 1 above)
-      const int rs = A.wy && my > 1 ? g.sy[(J0 + jt) * 3] - (J0 - 1) : jt;
-      for (int r = 0; r < 3; ++r) {
-        u0[r] = Uz[(m * NYH + rs + r) * NXH + l];
-        u1[r] = Uz[(m * NYH + rs + r) * NXH + l + 1];
-        w0[r] = Wz[(m * NYH + rs + r) * NXH + l];
-        w1[r] = Wz[((m + 1) * NYH + rs + r) * NXH + l];
+    // ---- Y: items (level m, tile row jt) of the halo column yl
+    if (yon) {
+      const int l = yl;
+      const T iHX = tIHX[l];
+      for (int jt = yg, m = 0;; jt += yn) {
+        while (jt >= TJv) jt -= TJv, ++m;
+        if (m >= mz) break;
+        T u0[3], u1[3], w0[3], w1[3];
+        // first stencil row of tile row jt (centred unless next to a y wall)
+        // (M_y = 1: the centred rows, as for M_x = 1 above)
+        const int rs = A.wy && my > 1 ? g.sy[(J0 + jt) * 3] - (J0 - 1) : jt;
+        const T* const pu = Uz + (m * NYH + rs) * NXS + l;
+        const T* const pw = Wz + (m * NYH + rs) * NXS + l;
+        for (int r = 0; r < 3; ++r) {
+          u0[r] = pu[r * NXS];
+          u1[r] = pu[r * NXS + 1];
+          w0[r] = pw[r * NXS];
+          w1[r] = pw[(NYH + r) * NXS];
+        }
+        const T ihz = ihzK[m];
+        T vv = Vz[(m * NYH + jt + 1) * NXS + l];
+        T* const ou = Uzy + (m * RY + jt * my) * NXS + l;
+        T* const ow = Wzy + (m * RY + jt * my) * NXS + l;
+        T* const ov = Vzy + (m * TJ + jt) * (my + 1) * NXS + l;
+        const T* R = tRy + 3 * jt * my;
+        const T* hy = tHy + jt * my;
+        for (int q = 0; q < my; ++q, R += 3) {
+          const T a = rdot3(R, u0), bb = rdot3(R, u1), c = rdot3(R, w0), d = rdot3(R, w1);
+          ou[q * NXS] = a;
+          if (l == NXH - 2) ou[q * NXS + 1] = bb;
+          ov[q * NXS] = vv;
+          ow[q * NXS] = c;
+          if (m == mz - 1) ow[(RY + q) * NXS] = d;
+          if (q < my - 1) vv = vv - hy[q] * ((bb - a) * iHX + (d - c) * ihz);
+        }
+        ov[my * NXS] = Vz[(m * NYH + jt + 2) * NXS + l];
       }
-      const T iHX = tIHX[l], ihz = ihzK[m];
-      T vv = Vz[(m * NYH + jt + 1) * NXH + l];
-      for (int q = 0; q < my; ++q) {
-        const int row = jt * my + q;
-        const T* R = tRy + 3 * row;
-        const T a = rdot3(R, u0), bb = rdot3(R, u1), c = rdot3(R, w0), d = rdot3(R, w1);
-        Uzy[(m * RY + row) * NXH + l] = a;
-        if (l == NXH - 2) Uzy[(m * RY + row) * NXH + l + 1] = bb;
-        Vzy[((m * TJ + jt) * (my + 1) + q) * NXH + l] = vv;
-        Wzy[(m * RY + row) * NXH + l] = c;
-        if (m == mz - 1) Wzy[(mz * RY + row) * NXH + l] = d;
-        if (q < my - 1) vv = vv - tHy[row] * ((bb - a) * iHX + (d - c) * ihz);
-      }
-      Vzy[((m * TJ + jt) * (my + 1) + my) * NXH + l] = Vz[(m * NYH + jt + 2) * NXH + l];
     }
     // publish the next layer's z tables into the other parity slot: its last
     // readers (stage z and x of layer K-1) are behind the barrier after stage z
@@ -381,48 +441,83 @@ __global__ void __launch_bounds__(256) refine_fused(RefArgs<T> A, int TI, int TJ
     // ---- X: items (dense row of the tile, level m) x 64 columns.  The next
     // layer's stage z writes only Uz, Vz, Wz, which stage x does not read, and
     // its tables sit in the other parity slot, so no barrier is needed after it.
-    const int npairs = TJv * my * mz;
-    for (int pr = grp; pr < npairs; pr += 4) {
-      if (!xon) continue;
-      const int m = pr % mz, row = pr / mz;
-      const int jt = row / my, q = row - jt * my;
-      const int i = Ix * mx + sub, j = (J0 + jt) * my + q, k = K * mz + m;
+    const int rows = TJv * my;
+    if (xon) for (int row = xg, m = 0;; row += xn) {
+      while (row >= rows) row -= rows, ++m;
+      if (m >= mz) break;
+      const int jt = my <= 64 ? (int)((row * imy) >> 16) : row / my;
+      const int i = Ix * mx + sub, j = J0 * my + row, k = K * mz + m;
+      const T* const pv = Vzy + (m * TJ * (my + 1) + row + jt) * NXS;
+      const T* const pw = Wzy + (m * RY + row) * NXS;
       T v0[3], v1[3], w0[3], w1[3];
       for (int r = 0; r < 3; ++r) {
-        v0[r] = Vzy[((m * TJ + jt) * (my + 1) + q) * NXH + xloc[r]];
-        v1[r] = Vzy[((m * TJ + jt) * (my + 1) + q + 1) * NXH + xloc[r]];
-        w0[r] = Wzy[(m * RY + row) * NXH + xloc[r]];
-        w1[r] = Wzy[((m + 1) * RY + row) * NXH + xloc[r]];
+        v0[r] = pv[xloc[r]];
+        v1[r] = pv[NXS + xloc[r]];
+        w0[r] = pw[xloc[r]];
+        w1[r] = pw[RY * NXS + xloc[r]];
       }
       const T ihy = tIhy[row], ihz = ihzK[m];
-      // the x march up to this sub-column, in the order of stage_x
-      T uu = Uzy[(m * RY + row) * NXH + (col / mx) + 1];
-      for (int mp = 0; mp < sub; ++mp) {
-        const T* Rp = tRx + 3 * (col - sub + mp);
-        const T ap = rdot3(Rp, v0), bp = rdot3(Rp, v1), cp = rdot3(Rp, w0), dp = rdot3(Rp, w1);
-        uu = uu - tHx[col - sub + mp] * ((bp - ap) * ihy + (dp - cp) * ihz);
-      }
-      const T* R = tRx + 3 * col;
-      const T a = rdot3(R, v0), c = rdot3(R, w0);
+      T uu = Uzy[(m * RY + row) * NXS + xc + 1];
       const int o = k * nxy + j * nx + i;
       // NT: the dense faces are written once, so streaming stores keep L2 for
       // the coarse halo; used when the tile's rows are whole 128-byte lines
       // (partial lines stored that way were 37% slower at M_x = 3).  A compile-
       // time flag: a runtime branch lets the compiler merge the two stores and
       // drop the streaming hint.
-      if constexpr (NT) {
-        __builtin_nontemporal_store(uu, A.out0 + o);
-        __builtin_nontemporal_store(a, A.out1 + o);
-        __builtin_nontemporal_store(c, A.out2 + o);
-        if (k == nz - 1) __builtin_nontemporal_store(rdot3(R, w1), A.out2 + o + nxy);
+      if constexpr (MX > 0) {
+        // the x march of the coarse cell up to this lane's last sub-column, in
+        // the order of stage_x
+        const T* const Rc = tRx + 3 * (col - sub);
+        const T* const hc = tHx + (col - sub);
+        Pack<T, PC> su, sv, sw;
+        if (PC < MX && sub > 0) {
+#pragma unroll
+          for (int q = 0; q < MX - PC; ++q) {
+            const T* R = Rc + 3 * q;
+            const T a = rdot3(R, v0), bp = rdot3(R, v1), c = rdot3(R, w0), dp = rdot3(R, w1);
+            uu = uu - hc[q] * ((bp - a) * ihy + (dp - c) * ihz);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < PC; ++q) {
+          const T* R = Rc + 3 * (sub + q);
+          const T a = rdot3(R, v0), c = rdot3(R, w0);
+          su.v[q] = uu;
+          sv.v[q] = a;
+          sw.v[q] = c;
+          if (q < PC - 1) {
+            const T bp = rdot3(R, v1), dp = rdot3(R, w1);
+            uu = uu - hc[sub + q] * ((bp - a) * ihy + (dp - c) * ihz);
+          }
+        }
+        store_pack<NT>(A.out0 + o, su);
+        store_pack<NT>(A.out1 + o, sv);
+        store_pack<NT>(A.out2 + o, sw);
+        if (k == nz - 1) {
+          Pack<T, PC> st;
+#pragma unroll
+          for (int q = 0; q < PC; ++q) st.v[q] = rdot3(tRx + 3 * (col + q), w1);
+          store_pack<NT>(A.out2 + o + nxy, st);
+        }
       } else {
-        A.out0[o] = uu;
-        A.out1[o] = a;
-        A.out2[o] = c;
-        if (k == nz - 1) A.out2[o + nxy] = rdot3(R, w1);
+        // the x march up to this sub-column, in the order of stage_x
+        for (int mp = 0; mp < sub; ++mp) {
+          const T* Rp = tRx + 3 * (col - sub + mp);
+          const T ap = rdot3(Rp, v0), bp = rdot3(Rp, v1), cp = rdot3(Rp, w0), dp = rdot3(Rp, w1);
+          uu = uu - tHx[col - sub + mp] * ((bp - ap) * ihy + (dp - cp) * ihz);
+        }
+        const T* R = tRx + 3 * col;
+        const T a = rdot3(R, v0), c = rdot3(R, w0);
+        Pack<T, 1> su{uu}, sv{a}, sw{c};
+        store_pack<NT>(A.out0 + o, su);
+        store_pack<NT>(A.out1 + o, sv);
+        store_pack<NT>(A.out2 + o, sw);
+        if (k == nz - 1) {
+          Pack<T, 1> st{rdot3(R, w1)};
+          store_pack<NT>(A.out2 + o + nxy, st);
+        }
       }
     }
-    cur = nxt;
   }
 }
 
@@ -1075,12 +1170,15 @@ hipError_t ensure(void** buf, size_t* have, size_t need) {
 
 constexpr int kFusedRows = 6;       // most coarse rows per tile
 constexpr int kFusedWgs = 8192;     // workgroups the layer split aims for
-constexpr int kFusedMinKc = 4;      // fewest coarse layers per workgroup
+// fewest coarse layers per workgroup: 4 share the table set-up and the first
+// layer's loads; fewer where 4 leave less than 2 workgroups a CU (64^3: 25 us
+// with 4 layers, 12 with one)
+constexpr int kFusedMinKc = 4;
 
 // LDS bytes of refine_fused for a tile of TI x TJ coarse cells.
 template <typename T>
 size_t fused_lds(int TI, int TJ, int mx, int my, int mz) {
-  return sizeof(T) * (size_t)(fused_tables(TI, TJ, mx, my) + fused_fields(TI, TJ, my, mz));
+  return sizeof(T) * (size_t)(fused_tables(TI, TJ, mx, my) + fused_fields(TJ, mx, my, mz));
 }
 
 // The time interpolation of the coarse velocity (Eq. 21, read as the linear
@@ -1122,7 +1220,7 @@ hipError_t refine_t(mr_ctx* c, const Geom<T>& g, const void* U, const void* V, c
   }
   const int64_t ncl = (int64_t)c->ncx * c->ncy * c->ncz, ncw = ncl + (int64_t)c->ncx * c->ncy;
   const int64_t nbl = U1 ? 2 * ncl + ncw : 0;   // the blended coarse level, at the buffer's start
-  int TI = kFuseCols / c->mx;
+  int TI = fuse_cols(c->mx) / c->mx;
   int TJ = 0;
   // a walled axis needs every tile (the last one included) to hold at least
   // two cells along it, so that the one-sided stencils stay inside the halo
@@ -1168,7 +1266,8 @@ hipError_t refine_t(mr_ctx* c, const Geom<T>& g, const void* U, const void* V, c
     // (at least kFusedMinKc layers each, so that the table set-up and the first
     // layer's loads are shared by a few layers)
     int nkc = (int)std::max<int64_t>(1, std::min<int64_t>(c->ncz, (kFusedWgs + tiles - 1) / tiles));
-    nkc = std::min(nkc, std::max(1, c->ncz / kFusedMinKc));
+    const int least = (int)std::max<int64_t>(1, std::min<int64_t>(kFusedMinKc, tiles * c->ncz / 512));
+    nkc = std::min(nkc, std::max(1, c->ncz / least));
     const int KC = (c->ncz + nkc - 1) / nkc;
     nkc = (c->ncz + KC - 1) / KC;
     const int64_t nb = tiles * nkc;
@@ -1176,10 +1275,18 @@ hipError_t refine_t(mr_ctx* c, const Geom<T>& g, const void* U, const void* V, c
     const size_t lds = fused_lds<T>(TI, TJ, c->mx, c->my, c->mz);
     const bool nt = (TI * c->mx * sizeof(T)) % 128 == 0 && (c->nx * sizeof(T)) % 128 == 0;
     const dim3 grid((unsigned)nb), block(256);
-    if (nt)
-      hipLaunchKernelGGL((refine_fused<T, true>), grid, block, lds, s, a, TI, TJ, nbx, nby, KC);
-    else
-      hipLaunchKernelGGL((refine_fused<T, false>), grid, block, lds, s, a, TI, TJ, nbx, nby, KC);
+    const auto run = [&](auto mx) {
+      constexpr int MX = decltype(mx)::value;
+      if (nt) hipLaunchKernelGGL((refine_fused<T, MX, true>), grid, block, lds, s, a, TI, TJ, nbx, nby, KC);
+      else hipLaunchKernelGGL((refine_fused<T, MX, false>), grid, block, lds, s, a, TI, TJ, nbx, nby, KC);
+    };
+    switch (c->mx) {
+      case 1: run(std::integral_constant<int, 1>()); break;
+      case 2: run(std::integral_constant<int, 2>()); break;
+      case 3: run(std::integral_constant<int, 3>()); break;
+      case 4: run(std::integral_constant<int, 4>()); break;
+      default: run(std::integral_constant<int, 0>()); break;
+    }
     return hipGetLastError();
   }
   T* Uz = (T*)c->interp_tmp + nbl;
