@@ -187,7 +187,10 @@ int mr_divergence(mr_ctx* ctx, const void* u, const void* v, const void* w,
  * values left out enter the solution with a share below 7e-18 (FP64) or 1e-14
  * (FP32), less than the rounding of the stored type.  (A column that holds a
  * NaN or Inf therefore becomes non-finite from its look-ahead below, not whole,
- * in one step.)  Otherwise one fused line-solver kernel, or with
+ * in one step.)  Steps with side walls, fourth-order faces or an explicit z
+ * share stream the same way on x and y of uniform widths from 2.5e6 cells on
+ * (FP64 with an odd N_x: 4.5e6), and on grids of few columns taller than 128
+ * levels.  Otherwise one fused line-solver kernel, or with
  * step_method 2 (and on columns taller than 640 levels) one column sweep and
  * its back substitution (see mr_scalar_steps). */
 int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_cur, void* th_next,

@@ -1,7 +1,7 @@
 // Host side of the streaming step: how a context's grid is cut into tiles and
 // z segments, and the launches (kernels in stream_kernel.h, instantiated in
 // k_stream64.hip and k_stream32.hip).
-#include "stream_kernel.h"
+#include "stream_variant.h"
 
 #include <algorithm>
 
@@ -11,6 +11,8 @@ extern template hipError_t launch_stream<double, false>(int, int, dim3, const St
 extern template hipError_t launch_stream<double, true>(int, int, dim3, const StreamArgs<double>&, hipStream_t);
 extern template hipError_t launch_stream<float, false>(int, int, dim3, const StreamArgs<float>&, hipStream_t);
 extern template hipError_t launch_stream<float, true>(int, int, dim3, const StreamArgs<float>&, hipStream_t);
+extern template hipError_t launch_stream_var<double>(int, int, dim3, const VarArgs<double>&, hipStream_t);
+extern template hipError_t launch_stream_var<float>(int, int, dim3, const VarArgs<float>&, hipStream_t);
 }  // namespace stream
 
 // Tile shape and number of z segments: the pair with the least time by a model
@@ -25,7 +27,9 @@ extern template hipError_t launch_stream<float, true>(int, int, dim3, const Stre
 // idle or a second round for half of them).  400^3 FP64: 256 x 4 and 1 segment
 // 587 us, 128 x 4 692; 576^3 FP64: 192 x 4 1.83 ms, 256 x 4 2.06; 450 x 300 x
 // 200 FP32: 192 x 4 154 us, 128 x 4 183 (300 workgroups on 256 CUs).
-StreamPlan stream_plan(int nx, int ny, int nz, bool f64, int cus, int depth, const std::vector<int> (&before)[2],
+// Variants (walls, fourth order, explicit z): 186^3 FP64 192 x 4 columns and 4
+// segments 66 us, 3 segments 76, 64 x 4 and 3 segments 68; 128 x 4 and 5, 82.
+StreamPlan stream_plan(int nx, int ny, int nz, bool f64, bool variant, int cus, int depth, const std::vector<int> (&before)[2],
                        const std::vector<int> (&after)[2]) {
   struct Shape {
     double one_us;    // a level of the only workgroup of a CU
@@ -34,12 +38,17 @@ StreamPlan stream_plan(int nx, int ny, int nz, bool f64, int cus, int depth, con
   };
   static const Shape s64[kStreamShapes] = {{1.40, 1.40, 5.6e6}, {1.13, 1.13, 5.5e6}, {0.72, 0.72, 5.35e6}, {0.60, 0.33, 5.0e6}};
   static const Shape s32[kStreamShapes] = {{0.70, 0.70, 5.6e6}, {0.70, 0.60, 5.5e6}, {0.61, 0.38, 5.35e6}, {0.55, 0.25, 5.0e6}};
-  const Shape* sh = f64 ? s64 : s32;
+  // the variants' kernels (three shapes; FP64 with 4-byte copies takes 1.6 times as long a level)
+  static const Shape v64[kStreamShapes] = {{}, {0.95, 0.95, 5.5e6}, {0.68, 0.68, 5.5e6}, {0.60, 0.42, 5.0e6}};
+  static const Shape v32[kStreamShapes] = {{}, {0.70, 0.62, 5.5e6}, {0.55, 0.45, 5.35e6}, {0.48, 0.22, 5.0e6}};
+  const double slow = variant && f64 && nx % 2 ? 1.6 : 1.0;
+  const Shape* sh = variant ? (f64 ? v64 : v32) : (f64 ? s64 : s32);
   const double sz = f64 ? 8.0 : 4.0;
   StreamPlan best;
   double best_us = -1.0;
   for (int q = 0; q < kStreamShapes; ++q) {
-    if (!stream_fits(kStreamDepth[depth], kStreamShape[q].segs * kStreamShape[q].rows)) continue;
+    const int waves = kStreamShape[q].segs * kStreamShape[q].rows;
+    if (!(variant ? stream_var_fits(kStreamDepth[depth], waves) : stream_fits(kStreamDepth[depth], waves))) continue;
     const int tw = 64 * kStreamShape[q].segs, rows = kStreamShape[q].rows;
     const int64_t ntx = (nx + tw - 1) / tw, nty = (ny + rows - 1) / rows;
     const double cols = (double)nx * ny;
@@ -62,7 +71,7 @@ StreamPlan stream_plan(int nx, int ny, int nz, bool f64, int cus, int depth, con
         }
       const double per_cu = (double)((ntx * nty * nseg + cus - 1) / cus);   // of the fullest CU
       const double mem = (5.0 * walked + nz) * loaded * sz / sh[q].rate;
-      const double us = std::max(mem, (levels + 6) * std::max(sh[q].one_us, per_cu * sh[q].more_us));
+      const double us = std::max(mem, (levels + 6) * slow * std::max(sh[q].one_us, per_cu * sh[q].more_us));
       if (best_us < 0.0 || us < best_us) {
         best_us = us;
         best = p;
@@ -157,7 +166,49 @@ hipError_t bwd_t(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* o
   return launch<T, true>(c, a, s);
 }
 
+template <typename T>
+hipError_t var_t(mr_ctx* c, const Geom<T>& g, int64_t n, const void* thp, const void* thc, void* out, const void* u,
+                 const void* v, const void* w, hipStream_t s) {
+  const int kind = step_kind(n, c->n_avg);
+  VarArgs<T> a;
+  ::memset((void*)&a, 0, sizeof(a));
+  a.f = (const T*)thc;
+  a.p = (const T*)thp;
+  a.u = (const T*)u;
+  a.v = (const T*)v;
+  a.w = (const T*)w;
+  a.out = (T*)out;
+  a.row = (const VarRow<T>*)c->vrow[kind];
+  a.cb = c->vcb[kind];
+  a.seg = c->stream_seg[0];
+  a.c4x = c->face_order == 4 ? g.c4x : nullptr;
+  a.c4y = c->face_order == 4 ? g.c4y : nullptr;
+  a.ap = (T)alpha_prev(kind);
+  a.ac = (T)alpha_cur(kind);
+  a.tx = (T)(c->tau[kind] * c->uhx);
+  a.ty = (T)(c->tau[kind] * c->uhy);
+  a.kx = (T)(c->tau[kind] * c->kappa * c->uhx * c->uhx);
+  a.ky = (T)(c->tau[kind] * c->kappa * c->uhy * c->uhy);
+  a.nx = c->nx;
+  a.ny = c->ny;
+  a.nz = c->nz;
+  const StreamShape sh = kStreamShape[c->stream_shape];
+  a.ntx = (c->nx + 64 * sh.segs - 1) / (64 * sh.segs);
+  a.nty = (c->ny + sh.rows - 1) / sh.rows;
+  a.band = std::min(8, a.ntx);
+  a.wx = c->wx;
+  a.wy = c->wy;
+  const dim3 grid((unsigned)((int64_t)a.ntx * a.nty * c->stream_nseg));
+  return launch_stream_var<T>(c->stream_shape, c->stream_v - 1, grid, a, s);
+}
+
 }  // namespace
+
+hipError_t launch_stream_step_var(mr_ctx* c, int64_t n, const void* thp, const void* thc, void* out, const void* u,
+                                  const void* v, const void* w, hipStream_t s) {
+  return c->precision == MR_FP64 ? var_t<double>(c, c->g64, n, thp, thc, out, u, v, w, s)
+                                 : var_t<float>(c, c->g32, n, thp, thc, out, u, v, w, s);
+}
 
 hipError_t launch_stream_step(mr_ctx* c, int64_t n, int q, const void* thp, const void* thc, void* out,
                               const void* u, const void* v, const void* w, hipStream_t s) {

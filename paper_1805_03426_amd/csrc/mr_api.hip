@@ -380,6 +380,26 @@ int reach_behind(const vector<double>& a, int s, double eps) {
   return d;
 }
 
+// Lz0 rows (a Dirichlet wall adds to the diagonal; its wall value is the
+// separate source b_z), padded with zeros to n.
+struct LzRows {
+  vector<double> lo, di, hi;
+};
+LzRows lz0_rows(const Axis& z, const mr_desc* d, int n) {
+  const int nz = z.n;
+  const vector<double>&h = z.h, &dc = z.dc;
+  LzRows r{vector<double>(n, 0.0), vector<double>(n, 0.0), vector<double>(n, 0.0)};
+  for (int k = 0; k < nz; ++k) {
+    r.lo[k] = k > 0 ? 1.0 / (h[k] * dc[k]) : 0.0;
+    r.hi[k] = k < nz - 1 ? 1.0 / (h[k] * dc[k + 1]) : 0.0;
+    double dg = -(r.lo[k] + r.hi[k]);
+    if (k == 0 && d->bc_bot == MR_DIRICHLET) dg -= 1.0 / (h[0] * dc[0]);
+    if (k == nz - 1 && d->bc_top == MR_DIRICHLET) dg -= 1.0 / (h[nz - 1] * dc[nz]);
+    r.di[k] = dg;
+  }
+  return r;
+}
+
 // One system's streaming tables in one walk direction, by walk position.
 struct StreamHost {
   vector<double> m, a, cb;
@@ -424,6 +444,32 @@ vector<mr::StreamRow<T>> stream_rows(const Axis& z, const SweepHost& h, const St
         o.c2 = (T)((down ? hi : lo) != 0.0);
       }
     }
+  }
+  return r;
+}
+
+// The variants' streaming rows of one step kind (tau), by walk position.
+template <typename T>
+vector<mr::VarRow<T>> variant_rows(const Problem& P, const mr_desc* d, const SweepHost& h, double tau) {
+  const Axis& z = P.z;
+  const int nz = z.n;
+  vector<mr::VarRow<T>> r((size_t)nz + 2 * mr::kStreamRowPad);
+  memset((void*)r.data(), 0, r.size() * sizeof(r[0]));
+  const vector<double> w4 = face_weights4(z);
+  const LzRows lz = lz0_rows(z, d, nz);
+  const double tkw = tau * P.kappa * d->z_explicit;
+  for (int k = 0; k < nz; ++k) {
+    mr::VarRow<T>& c = r[(size_t)k + 2 + mr::kStreamRowPad];   // closes level k
+    c.em = h.up_m[k];
+    c.ea = h.up_a[k];
+    c.tkb = h.tkb[k];
+    c.tz = (T)(tau / z.h[k]);
+    mr::VarRow<T>& o = r[(size_t)k + 1 + mr::kStreamRowPad];   // face k and level k's explicit share
+    for (int q = 0; q < 4 && k > 0; ++q)
+      o.cz[q] = (T)(d->face_order == 4 ? w4[(size_t)k * 4 + q] : (q == 1 || q == 2 ? 0.5 : 0.0));
+    o.lz[0] = (T)(tkw * lz.lo[k]);
+    o.lz[1] = (T)(tkw * lz.di[k]);
+    o.lz[2] = (T)(tkw * lz.hi[k]);
   }
   return r;
 }
@@ -521,20 +567,10 @@ GeomOffsets pack_geom(Packer& pk, const Problem& P, const mr_desc* d, const vect
   }
   o.zlo = pk.put(cast<T>(lo));
   o.zhi = pk.put(cast<T>(hi));
-  // Lz0 rows and their transpose (a Dirichlet wall adds to the diagonal; its
-  // wall value is the separate source b_z)
   const int nz = P.z.n;
-  const vector<double>& h = P.z.h;
-  const vector<double>& dc = P.z.dc;
-  vector<double> zl(npad, 0.0), zd(npad, 0.0), zh(npad, 0.0), ztl(npad, 0.0), zth(npad, 0.0);
-  for (int k = 0; k < nz; ++k) {
-    zl[k] = k > 0 ? 1.0 / (h[k] * dc[k]) : 0.0;
-    zh[k] = k < nz - 1 ? 1.0 / (h[k] * dc[k + 1]) : 0.0;
-    double dg = -(zl[k] + zh[k]);
-    if (k == 0 && d->bc_bot == MR_DIRICHLET) dg -= 1.0 / (h[0] * dc[0]);
-    if (k == nz - 1 && d->bc_top == MR_DIRICHLET) dg -= 1.0 / (h[nz - 1] * dc[nz]);
-    zd[k] = dg;
-  }
+  const LzRows lz = lz0_rows(P.z, d, npad);
+  const vector<double>&zl = lz.lo, &zd = lz.di, &zh = lz.hi;
+  vector<double> ztl(npad, 0.0), zth(npad, 0.0);   // the transpose
   for (int k = 0; k < nz; ++k) {
     ztl[k] = k > 0 ? zh[k - 1] : 0.0;
     zth[k] = k < nz - 1 ? zl[k + 1] : 0.0;
@@ -765,6 +801,20 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   const bool streams = P.sweep_ok && desc->step_method == 0 &&
                        (nch == 0 || (int64_t)P.x.n * P.y.n * nz >= 4500000 ||
                         (f64 && P.x.n % 2 == 0 && !(one_round && nz <= 64)));
+  // the variants' forward step streams (x and y of uniform widths) on grids of
+  // 2.5e6 cells and more (FP64 with 4-byte copies 4.5e6) and on tall columns in
+  // one round of tiles.  One step in us, line solver against streaming, with walls,
+  // fourth order and explicit z / with walls alone: FP64 186^3 132 and 76 / 105
+  // and 75, 250^3 270 and 153 / 234 and 149, 300 x 280 x 30 44 and 31 / 39 and 31,
+  // 64 x 64 x 256 56 and 28 / 41 and 27, 128^3 33 and 31 / 27 and 31, 160 x 160 x
+  // 64 30 and 26 / 25 and 26, 64^3 19 and 17 / 14 and 17; FP32 186^3 77 and 42 /
+  // 53 and 42, 300 x 280 x 30 24 and 23 / 21 and 23, 160 x 160 x 64 20 and 19 / 16
+  // and 18; FP64 odd: 187^3 134 and 82 / 106 and 81, 301 x 280 x 30 44 and 45 / 39
+  // and 45
+  const bool copies4 = f64 && P.x.n % 2 != 0;
+  const bool streamv = !P.sweep_ok && desc->step_method == 0 && nch > 0 && uniform_axis(P.x) && uniform_axis(P.y) &&
+                       ((int64_t)P.x.n * P.y.n * nz >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));
+  size_t vro[mr::NKINDS], vcbo[mr::NKINDS];
   size_t sro[2][2][mr::NKINDS], scbo[2][2][mr::NKINDS];   // streaming tables: [transposed][down][kind]
   const double eps = f64 ? mr::kTruncate64 : mr::kTruncate32;
   int ahead = 0;                                      // the streaming step's look-ahead
@@ -796,6 +846,16 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     for (int k = 0; k < nz; ++k) sh.tkb[k] = tk * bz[k];
     swo[kind] = pack_sweep(pk, sh);
     pack_stream(sh, kind, false);
+    if (streamv) {
+      const StreamHost w = stream_walk(sh, false);
+      vro[kind] = f64 ? pk.put(variant_rows<double>(P, desc, sh, tau)) : pk.put(variant_rows<float>(P, desc, sh, tau));
+      vcbo[kind] = pk.put(stream_cb(w));
+      for (int k = 0; k < nz; ++k) {
+        after[0][k] = std::max(after[0][k], reach_ahead(w.cb, k, eps));
+        before[0][k] = std::max(before[0][k], reach_behind(w.a, k, eps));
+        ahead = std::max(ahead, after[0][k]);
+      }
+    }
     // transpose: sub^T_k = sup_{k-1}, sup^T_k = sub_{k+1}
     for (int k = 0; k < nz; ++k) {
       tsub[k] = k > 0 ? sup[k - 1] : 0.0;
@@ -826,10 +886,10 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   // the streaming step's look-ahead, tiles and z segments
   int stream_d = 0;
   mr::StreamPlan plan;
-  if (streams) {
+  if (streams || streamv) {
     for (int d = mr::kStreamDepths; d > 0; --d)
       if (ahead <= mr::kStreamDepth[d - 1]) stream_d = d;
-    if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, cus, stream_d - 1, before, after);
+    if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, streamv, cus, stream_d - 1, before, after);
   }
   const size_t o_seg[2] = {pk.put(plan.seg[0]), pk.put(plan.seg[1])};
   vector<double> dcz(P.z.dc);
@@ -905,11 +965,17 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   const bool fills = tiles * sh.segs * sh.rows >= 16 * (int64_t)cus && (rounds == 1 || 4 * tiles >= 3 * rounds * slots);
   c->sweep_pref = desc->step_method == 2 || (desc->step_method == 0 && P.sweep_ok && (nch == 0 || fills));
   c->sweep_single = nch == 0 || desc->step_method == 2;
-  c->stream_d = stream_d;
+  c->stream_d = streams ? stream_d : 0;
+  c->stream_v = streamv ? stream_d : 0;
   c->stream_shape = plan.shape;
   c->stream_nseg = plan.nseg;
   for (int d = 0; d < 2; ++d) c->stream_seg[d] = (const int*)(base + o_seg[d]);
-  for (int k = 0; k < mr::NKINDS && stream_d; ++k)
+  for (int k = 0; k < mr::NKINDS && c->stream_v; ++k) {
+    const size_t row = f64 ? sizeof(mr::VarRow<double>) : sizeof(mr::VarRow<float>);
+    c->vrow[k] = base + vro[k] + mr::kStreamRowPad * row;
+    c->vcb[k] = (const double*)(base + vcbo[k]) + mr::kStreamPad;
+  }
+  for (int k = 0; k < mr::NKINDS && c->stream_d; ++k)
     for (int r = 0; r < 2; ++r)
       for (int d = 0; d < 2; ++d) {
         const double* cb = (const double*)(base + scbo[r][d][k]) + mr::kStreamPad;
@@ -979,6 +1045,10 @@ int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_c
                                      as_stream(stream)));
     return MR_OK;
   }
+  if (ctx->stream_v) {
+    MR_LAUNCH(mr::launch_stream_step_var(ctx, n, thp, th_cur, th_next, u, v, w, as_stream(stream)));
+    return MR_OK;
+  }
   if (ctx->sweep_single) {
     // one column sweep and its back substitution
     void* outs[1] = {th_next};
@@ -1007,6 +1077,14 @@ int mr_scalar_steps(mr_ctx* ctx, int64_t n0, int32_t count, const void* th_prev,
       const void* a = q >= 2 ? outs[q - 2] : (q == 1 ? th_cur : thp);
       const void* b = q >= 1 ? outs[q - 1] : th_cur;
       MR_LAUNCH(mr::launch_stream_step(ctx, n0 + q, ctx->sweep_pref ? q : -1, a, b, outs[q], u, v, w, s));
+    }
+    return MR_OK;
+  }
+  if (ctx->stream_v) {
+    for (int32_t q = 0; q < count; ++q) {
+      const void* a = q >= 2 ? outs[q - 2] : (q == 1 ? th_cur : thp);
+      const void* b = q >= 1 ? outs[q - 1] : th_cur;
+      MR_LAUNCH(mr::launch_stream_step_var(ctx, n0 + q, a, b, outs[q], u, v, w, s));
     }
     return MR_OK;
   }
@@ -1212,7 +1290,8 @@ int mr_coarse_step(mr_ctx* ctx, int64_t n0, int32_t mt, const void* U0, const vo
       while (o == c || o == p) ++o;   // the buffer holding neither level
       MR_LAUNCH(ctx->stream_d ? mr::launch_stream_step(ctx, n, ctx->sweep_pref ? i - 1 : -1, ring[p], ring[c], ring[o], u,
                                                        v, w, s)
-                              : mr::launch_step(ctx, n, ring[p], ring[c], ring[o], u, v, w, s));
+                : ctx->stream_v ? mr::launch_stream_step_var(ctx, n, ring[p], ring[c], ring[o], u, v, w, s)
+                                : mr::launch_step(ctx, n, ring[p], ring[c], ring[o], u, v, w, s));
       p = c;
       c = o;
     }

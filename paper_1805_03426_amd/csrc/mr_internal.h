@@ -141,6 +141,20 @@ constexpr bool stream_fits(int levels, int waves) {
   return levels <= 28 || (levels <= 44 && waves <= 12) || waves <= 8;
 }
 
+// The same for the variants (side walls, fourth-order faces, explicit z share),
+// whose face weights and second level behind hold about 60 registers more.
+constexpr bool stream_var_fits(int levels, int waves) { return waves <= 8 || (waves <= 12 && levels <= 16); }
+
+// What the variants' streaming step needs when its walk reads level s: the
+// elimination and tau / h_z of level s - 2, the weights of the cells s-3 .. s in
+// the value on face s - 1 (zero on a wall), tau kappa w times the z diffusion's
+// row of level s - 1 (explicit share).
+template <typename T>
+struct alignas(64) VarRow {
+  double em, ea, tkb, unused;
+  T cz[4], lz[3], tz;
+};
+
 // A context's cut into tiles and segments; per walk direction and segment:
 // first position, end, walk start, walk end.
 struct StreamPlan {
@@ -149,7 +163,7 @@ struct StreamPlan {
 };
 // before[d][s] / after[d][s]: how far before / after position s of walk
 // direction d (0 up, 1 down) values still matter to the solution at s.
-StreamPlan stream_plan(int nx, int ny, int nz, bool f64, int cus, int depth, const std::vector<int> (&before)[2],
+StreamPlan stream_plan(int nx, int ny, int nz, bool f64, bool variant, int cus, int depth, const std::vector<int> (&before)[2],
                        const std::vector<int> (&after)[2]);
 template <typename T>
 struct StreamSys {
@@ -187,6 +201,10 @@ struct mr_ctx {
   // streaming-step factors: [transposed][walking down][step kind] (of the context's precision)
   mr::StreamSys<double> sr64[2][2][mr::NKINDS];
   mr::StreamSys<float> sr32[2][2][mr::NKINDS];
+  // the variants' forward step: rows and back factors per step kind
+  const void* vrow[mr::NKINDS];
+  const double* vcb[mr::NKINDS];
+  int stream_v;                    // as stream_d, of the variants' forward step (at most one of the two is set)
   int stream_d;                    // look-ahead of the streaming step: 1 + index into kStreamDepth (0: it does not apply)
   int stream_shape;                // its tile shape (index into kStreamShape)
   int stream_nseg;                 // z segments per column
@@ -258,6 +276,9 @@ hipError_t launch_sweep_seed(mr_ctx* c, int64_t n, const void* lam, void* out, h
 // sequence where the context would run column sweeps instead, else -1.
 hipError_t launch_stream_step(mr_ctx* c, int64_t n, int q, const void* thp, const void* thc, void* out,
                               const void* u, const void* v, const void* w, hipStream_t s);
+// The variants' streaming forward step (contexts with stream_v > 0).
+hipError_t launch_stream_step_var(mr_ctx* c, int64_t n, const void* thp, const void* thc, void* out, const void* u,
+                                  const void* v, const void* w, hipStream_t s);
 hipError_t launch_stream_step_backward(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* out,
                                        const void* u, const void* v, const void* w, hipStream_t s);
 // Grows the context's reduction scratch to at least `bytes`.
