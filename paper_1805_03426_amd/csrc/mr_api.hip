@@ -363,23 +363,23 @@ bool sweep_factors(int nz, const double* sub, const double* diag, const double* 
   return true;
 }
 
-// Number of walk positions after position s whose values still matter to the
-// solution at s (and before it, whose elimination values do): the shortest
-// distance over which the product of the recurrence's factors falls to eps.
-int reach_ahead(const vector<double>& cb, int s, double eps) {
-  const int n = (int)cb.size();
+// Number of walk positions after (cb) or before (a) each position whose values
+// still matter to its solution or elimination value: the shortest distance over
+// which the product of the recurrence's factors falls to eps.  `out` takes the
+// larger of itself and that; one product moves along with both ends.
+template <typename At, typename Out>
+void reach(int n, At factor, double eps, Out out) {
   double p = 1.0;
-  int d = 0;
-  while (s + d < n && p > eps) p *= fabs(cb[s + d++]);
-  return d;
+  int e = 0;   // p: the product of the factors s .. e-1
+  for (int s = 0; s < n; ++s) {
+    if (e < s) e = s, p = 1.0;
+    while (e < n && p > eps) p *= fabs(factor(e++));
+    out(s) = std::max(out(s), e - s);
+    const double f = fabs(factor(s));
+    if (f > 0.0 && p > 0.0) p /= f;
+    else e = s + 1, p = 1.0;   // (a zero factor ends every reach; start anew)
+  }
 }
-int reach_behind(const vector<double>& a, int s, double eps) {
-  double p = 1.0;
-  int d = 0;
-  while (s - d >= 0 && p > eps) p *= fabs(a[s - d++]);
-  return d;
-}
-
 // Lz0 rows (a Dirichlet wall adds to the diagonal; its wall value is the
 // separate source b_z), padded with zeros to n.
 struct LzRows {
@@ -820,17 +820,19 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   int ahead = 0;                                      // the streaming step's look-ahead
   vector<int> after[2], before[2];                    // its reach after / before each walk position
   for (int d = 0; d < 2; ++d) after[d].assign(nz, 0), before[d].assign(nz, 0);
+  // (`ahead` covers the walk directions and step kinds added so far)
+  auto add_reach = [&](const StreamHost& w, int d) {
+    reach(nz, [&](int k) { return w.cb[k]; }, eps, [&](int k) -> int& { return after[d][k]; });
+    reach(nz, [&](int k) { return w.a[nz - 1 - k]; }, eps, [&](int k) -> int& { return before[d][nz - 1 - k]; });
+    ahead = std::max(ahead, *std::max_element(after[d].begin(), after[d].end()));
+  };
   auto pack_stream = [&](const SweepHost& h, int kind, bool rev) {
     if (!streams) return;
     for (int d = 0; d < 2; ++d) {
       const StreamHost w = stream_walk(h, d);
       sro[rev][d][kind] = f64 ? pk.put(stream_rows<double>(P.z, h, w, rev, d)) : pk.put(stream_rows<float>(P.z, h, w, rev, d));
       scbo[rev][d][kind] = pk.put(stream_cb(w));
-      for (int k = 0; k < nz; ++k) {
-        after[d][k] = std::max(after[d][k], reach_ahead(w.cb, k, eps));
-        before[d][k] = std::max(before[d][k], reach_behind(w.a, k, eps));
-        ahead = std::max(ahead, after[d][k]);
-      }
+      add_reach(w, d);
     }
   };
   vector<double> sub(nz), diag(nz), sup(nz), bz(nz), tsub(nz), tsup(nz);
@@ -850,11 +852,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
       const StreamHost w = stream_walk(sh, false);
       vro[kind] = f64 ? pk.put(variant_rows<double>(P, desc, sh, tau)) : pk.put(variant_rows<float>(P, desc, sh, tau));
       vcbo[kind] = pk.put(stream_cb(w));
-      for (int k = 0; k < nz; ++k) {
-        after[0][k] = std::max(after[0][k], reach_ahead(w.cb, k, eps));
-        before[0][k] = std::max(before[0][k], reach_behind(w.a, k, eps));
-        ahead = std::max(ahead, after[0][k]);
-      }
+      add_reach(w, 0);
     }
     // transpose: sub^T_k = sup_{k-1}, sup^T_k = sub_{k+1}
     for (int k = 0; k < nz; ++k) {
