@@ -881,6 +881,12 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   shid.up_cb.assign(nz, 0.0); shid.dn_cb.assign(nz, 0.0);
   shid.tkb.assign(nz, 0.0);
   const SweepOffsets swido = pack_sweep(pk, shid);
+  size_t o_sid = 0, o_sidcb = 0;
+  if (streams) {
+    const StreamHost w = stream_walk(shid, false);
+    o_sid = f64 ? pk.put(stream_rows<double>(P.z, shid, w, true, false)) : pk.put(stream_rows<float>(P.z, shid, w, true, false));
+    o_sidcb = pk.put(stream_cb(w));
+  }
   // the streaming step's look-ahead, tiles and z segments
   int stream_d = 0;
   mr::StreamPlan plan;
@@ -968,6 +974,11 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   c->stream_shape = plan.shape;
   c->stream_nseg = plan.nseg;
   for (int d = 0; d < 2; ++d) c->stream_seg[d] = (const int*)(base + o_seg[d]);
+  if (c->stream_d) {
+    const double* cb = (const double*)(base + o_sidcb) + mr::kStreamPad;
+    c->sid64 = {(const mr::StreamRow<double>*)(base + o_sid) + mr::kStreamRowPad, cb};
+    c->sid32 = {(const mr::StreamRow<float>*)(base + o_sid) + mr::kStreamRowPad, cb};
+  }
   for (int k = 0; k < mr::NKINDS && c->stream_v; ++k) {
     const size_t row = f64 ? sizeof(mr::VarRow<double>) : sizeof(mr::VarRow<float>);
     c->vrow[k] = base + vro[k] + mr::kStreamRowPad * row;
@@ -1116,7 +1127,7 @@ int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const v
   MR_CALL_RANGE();
   if (!ctx || n < 0 || !mu_cur || !out || !u || !v || !w) return MR_EINVAL;
   if (out == mu_cur || (mu_next && out == mu_next) || (lam_add && out == lam_add)) return MR_EINVAL;
-  if (ctx->stream_d && n > 0 && !lam_add) {
+  if (ctx->stream_d && !lam_add) {
     MR_LAUNCH(mr::launch_stream_step_backward(ctx, n, mu_next, mu_cur, out, u, v, w, as_stream(stream)));
     return MR_OK;
   }

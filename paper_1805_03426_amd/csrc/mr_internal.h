@@ -201,6 +201,9 @@ struct mr_ctx {
   // streaming-step factors: [transposed][walking down][step kind] (of the context's precision)
   mr::StreamSys<double> sr64[2][2][mr::NKINDS];
   mr::StreamSys<float> sr32[2][2][mr::NKINDS];
+  // the reverse step 0's (walking up): the transposed stencil's rows and no solve
+  mr::StreamSys<double> sid64;
+  mr::StreamSys<float> sid32;
   // the variants' forward step: rows and back factors per step kind
   const void* vrow[mr::NKINDS];
   const double* vcb[mr::NKINDS];

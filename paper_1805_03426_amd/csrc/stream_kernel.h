@@ -55,6 +55,7 @@ struct StreamArgs {
   const double* cb;          // per walk position s: x_s = e_s - cb_s x_{s+1}; readable from -kStreamPad
   const int* seg;            // per z segment: first position, end, walk start, walk end
   T ap, ac, tau, tk;
+  T tk0;                     // reverse step 0: tau kappa of the start-up step's own diffusion (else 0)
   T uhx, uhy, uxx, uyy;
   int nx, ny, nz;
   int ntx, nty;              // tiles per level
@@ -273,6 +274,9 @@ __global__ void __launch_bounds__(64 * TX * TY) stream_kernel(StreamArgs<T> A) {
         adv = -half * ((u1 * (fc + fxp) - u0 * (fxm + fc)) * A.uhx + (v1 * (fc + fyp) - v0 * (fym + fc)) * A.uhy +
                        rc.c2 * wf * (tc + fc));
       rr = A.ap * pc + A.ac * fc + A.tau * adv + A.tk * (lx2 * A.uxx + ly2 * A.uyy);
+      if constexpr (REV)   // the start-up step reads theta^0 for its diffusion too
+        if (A.tk0 != T(0))
+          rr += A.tk0 * (fma_(T(-2), fc, fxp + fxm) * A.uxx + fma_(T(-2), fc, fyp + fym) * A.uyy);
     } else {
       const T x = fma_(u1, fc + fxp, -(u0 * (fxm + fc))), y = fma_(v1, fc + fyp, -(v0 * (fym + fc)));
       pxy = as_sweep ? fma_(x, A.uhx, y * A.uhy) : fma_(y, A.uhy, x * A.uhx);
