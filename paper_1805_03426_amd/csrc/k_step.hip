@@ -173,16 +173,17 @@ __global__ void __launch_bounds__(256) grad_kernel(GradArgs<T> A) {
 // Second-order faces: a workgroup of kGradRows wavefronts owns a tile of 64
 // columns by kGradRows rows and walks a run of consecutive z segments of ZS
 // levels.  For each segment and step in turn every wavefront loads theta and
-// mu of its row on the segment's levels, the first wavefront also the row
-// below the tile, and publishes them in LDS, where the wavefront of the next
+// mu of its row on the segment's levels and its share of the row below the
+// tile, and publishes them in LDS, where the wavefront of the next
 // row finds its y neighbours: a row is read from memory once per step and
 // segment (the y halo is one row in kGradRows).  The level below a segment is
 // loaded for the first segment of the run and then carried in registers from
 // the segment before (CARRY; without it, loaded for every segment).  The loads
 // of a step are independent of each other, so they are all in flight
-// together.  The column to the left comes from the lane beside it (lane 0
-// loads it).  The LDS buffer alternates from step to step, one barrier per
-// step.  Every step's contribution goes to per-level accumulators in
+// together; AHEAD: they are issued before the step before is added up.  The
+// column to the left comes from the lane beside it; one load of 2 ZS lanes
+// fetches the first lane's.  The LDS buffer alternates from step to step, one
+// barrier per step.  Every step's contribution goes to per-level accumulators in
 // registers; gu, gv, gw are updated once per level.
 // Timed at 1024x1024x512 against 16 rows (one workgroup of 139 KB of LDS per
 // CU): 8 rows, two workgroups per CU, were 7% faster in FP64 and level in FP32.
@@ -192,7 +193,17 @@ constexpr int kGradRows = 8;    // wavefronts (rows of 64 columns) per workgroup
 constexpr int kGradRun = 2;     // FP32: segments per workgroup
 constexpr int kGradWaves = 4;   // wavefronts per SIMD to fit (128 VGPRs)
 
-template <typename T, int KM, int ZS, bool CARRY>
+// Lane l's value, for the whole wavefront.
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+  const long long x = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)x, l);
+  return __longlong_as_double(((long long)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) | lo);
+}
+
+template <typename T, int KM, int ZS, bool CARRY, bool AHEAD>
 __global__ void __launch_bounds__(64 * kGradRows, kGradWaves) grad_seg(GradArgs<T> A, int run) {
   __shared__ T lt[2][ZS][kGradRows + 1][kWave];   // theta rows by step parity, level, tile row + 1
   __shared__ T lm[2][ZS][kGradRows + 1][kWave];   // mu rows
@@ -228,7 +239,12 @@ __global__ void __launch_bounds__(64 * kGradRows, kGradWaves) grad_seg(GradArgs<
   const int nxy = nx * ny;
   constexpr unsigned sz = sizeof(T);
   const unsigned oc = (unsigned)(j * nx + i) * sz;
-  const unsigned oxe = (unsigned)(j * nx + im) * sz;   // lane 0: its left column
+  // the left column of the row (lane l < ZS: of theta on the segment's level l,
+  // the next ZS lanes: of mu) and the row below the tile (items: theta on each
+  // level, then mu, dealt to the wavefronts)
+  const int el = lane < 2 * ZS ? lane % ZS : 0;
+  const int i0 = xt * kWave;
+  const unsigned oxe = (unsigned)(j * nx + (i0 == 0 ? (wx ? 0 : nx - 1) : i0 - 1)) * sz;
   const unsigned oh = (unsigned)(jh * nx + i) * sz;
   const T half = T(0.5);
   const T ihx = A.g.ihx[i], ihxm = A.g.ihx[im], ihy = A.g.ihy[j], ihym = A.g.ihy[jm];
@@ -238,10 +254,41 @@ __global__ void __launch_bounds__(64 * kGradRows, kGradWaves) grad_seg(GradArgs<
   };
   T cbt[CARRY ? KM : 1], cbm[CARRY ? KM : 1];   // each step's theta and mu on the level below the segment
   int p = 0;                                    // LDS buffer of the next step
+  // a step's values on the segment at level k0: levels k0-1 .. k0+ZS-1 of the
+  // wavefront's row (clamped into the grid; the ones outside add nothing; the
+  // level below only where it is not carried), the edge and the halo items
+  constexpr int HN = 2 * ZS / kGradRows;
+  struct Vals {
+    T tc[ZS + 1], mc[ZS + 1], edge, halo[HN];
+  };
+  auto fetch = [&](int s, int k0, bool below, Vals& v) {
+    const T* th = sptr[0][s];
+    const T* mu = sptr[1][s];
+    if (below) {
+      const int k = max(k0 - 1, 0);
+      v.tc[0] = at(th, k, oc);
+      v.mc[0] = at(mu, k, oc);
+    }
+#pragma unroll
+    for (int z = 1; z <= ZS; ++z) {
+      const int k = min(k0 + z - 1, nz - 1);
+      v.tc[z] = at(th, k, oc);
+      v.mc[z] = at(mu, k, oc);
+    }
+    v.edge = at(lane < ZS ? th : mu, min(k0 + el, nz - 1), oxe);
+#pragma unroll
+    for (int q = 0; q < HN; ++q) {
+      const int it = r + q * kGradRows;
+      v.halo[q] = at(it < ZS ? th : mu, min(k0 + it % ZS, nz - 1), oh);
+    }
+  };
+  Vals cur, nxt;
+  if constexpr (AHEAD) fetch(0, seg0 * ZS, true, cur);
   for (int sg = 0; sg < run; ++sg) {
     const int k0 = (seg0 + sg) * ZS;
     if (k0 >= nz) break;
-    const bool below = !CARRY || sg == 0;       // load the level below (else carried)
+    const bool below = !CARRY || sg == 0;       // the level below was loaded (else carried)
+    const bool more = sg + 1 < run && k0 + ZS < nz;
     T ihz[ZS + 1];   // 1/hz of the level below the segment and of its levels (scalar loads)
 #pragma unroll
     for (int z = 0; z <= ZS; ++z) {
@@ -254,48 +301,40 @@ __global__ void __launch_bounds__(64 * kGradRows, kGradWaves) grad_seg(GradArgs<
 #pragma unroll
     for (int s = 0; s < KM; ++s) {
       if (s < A.count) {
-        const T* th = sptr[0][s];
-        const T* mu = sptr[1][s];
         const T tau = stau[s];
-        // levels k0-1 .. k0+ZS-1 (clamped into the grid; the ones outside add nothing)
-        T tc[ZS + 1], mc[ZS + 1], te[ZS], me[ZS], th_h[ZS], mu_h[ZS];
-        if (below) {
-          const int k = max(k0 - 1, 0);
-          tc[0] = at(th, k, oc);
-          mc[0] = at(mu, k, oc);
-        } else if constexpr (CARRY) {
-          tc[0] = cbt[s];
-          mc[0] = cbm[s];
+        if constexpr (AHEAD) {
+          // the next step's values (the next segment's first step after the last), in
+          // flight while this one is added up
+          if (s + 1 < A.count) fetch(s + 1, k0, below, nxt);
+          else if (more) fetch(0, k0 + ZS, !CARRY, nxt);
+        } else {
+          fetch(s, k0, below, cur);
         }
-#pragma unroll
-        for (int z = 1; z <= ZS; ++z) {
-          const int k = min(k0 + z - 1, nz - 1);
-          tc[z] = at(th, k, oc);
-          mc[z] = at(mu, k, oc);
-          if (lane == 0) {
-            te[z - 1] = at(th, k, oxe);
-            me[z - 1] = at(mu, k, oxe);
-          }
-          if (r == 0) {
-            th_h[z - 1] = at(th, k, oh);
-            mu_h[z - 1] = at(mu, k, oh);
+        if constexpr (CARRY) {
+          if (!below) {
+            cur.tc[0] = cbt[s];
+            cur.mc[0] = cbm[s];
           }
         }
+        const T* const tc = cur.tc;
+        const T* const mc = cur.mc;
 #pragma unroll
         for (int z = 0; z < ZS; ++z) {
           lt[p][z][r + 1][lane] = tc[z + 1];
           lm[p][z][r + 1][lane] = mc[z + 1];
-          if (r == 0) {
-            lt[p][z][0][lane] = th_h[z];
-            lm[p][z][0][lane] = mu_h[z];
-          }
+        }
+#pragma unroll
+        for (int q = 0; q < HN; ++q) {
+          const int it = r + q * kGradRows;
+          (it < ZS ? lt : lm)[p][it % ZS][0][lane] = cur.halo[q];
         }
         __syncthreads();
 #pragma unroll
         for (int z = 0; z < ZS; ++z) {
           const T t = tc[z + 1], m = mc[z + 1];
           const T tl = line::lane_shr(t), ml = line::lane_shr(m);
-          const T txm = lane == 0 ? te[z] : tl, mxm = lane == 0 ? me[z] : ml;
+          const T txm = lane == 0 ? lane_value(cur.edge, z) : tl;
+          const T mxm = lane == 0 ? lane_value(cur.edge, ZS + z) : ml;
           const T ty = lt[p][z][r][lane], my = lm[p][z][r][lane];
           su[z] += tau * (half * (txm + t)) * (m * ihx - mxm * ihxm);
           sv[z] += tau * (half * (ty + t)) * (m * ihy - my * ihym);
@@ -306,6 +345,7 @@ __global__ void __launch_bounds__(64 * kGradRows, kGradWaves) grad_seg(GradArgs<
           cbm[s] = mc[ZS];
         }
         p ^= 1;
+        if constexpr (AHEAD) cur = nxt;
       }
     }
 #pragma unroll
@@ -321,19 +361,38 @@ __global__ void __launch_bounds__(64 * kGradRows, kGradWaves) grad_seg(GradArgs<
   }
 }
 
-// Segments of 8 levels in FP32 (runs of up to kGradRun segments, the level below
-// carried), of 4 in FP64 (no carry: its registers would not fit beside the
-// accumulators at 4 wavefronts per SIMD).
-template <typename T, int KM>
-void launch_grad_seg(mr_ctx* c, const GradArgs<T>& a, hipStream_t s) {
-  constexpr bool f64 = sizeof(T) == 8;
-  constexpr int ZS = f64 ? 4 : 8;   // levels per segment
+template <typename T, int KM, int ZS, bool CARRY, bool AHEAD>
+void launch_grad_form(mr_ctx* c, const GradArgs<T>& a, int most, hipStream_t s) {
   const int ntx = (c->nx + kWave - 1) / kWave, nty = (c->ny + kGradRows - 1) / kGradRows;
   const int nseg = (c->nz + ZS - 1) / ZS;
-  const int run = f64 ? 1 : std::min(nseg, kGradRun);
+  const int run = std::min(nseg, most);
   const int nrun = (nseg + run - 1) / run;
-  const dim3 grid((unsigned)((int64_t)ntx * nty * nrun)), block(kWave * kGradRows);   // 74 KB of LDS
-  hipLaunchKernelGGL((grad_seg<T, KM, ZS, !f64>), grid, block, 0, s, a, run);
+  const dim3 grid((unsigned)((int64_t)ntx * nty * nrun)), block(kWave * kGradRows);
+  hipLaunchKernelGGL((grad_seg<T, KM, ZS, CARRY, AHEAD>), grid, block, 0, s, a, run);
+}
+
+// FP64: segments of 4 levels, the next step's loads ahead, no carry (its
+// registers would not fit beside the accumulators at 4 wavefronts per SIMD):
+// 256^3, 3, 5 and 10 steps 358, 494 and 834 us against 380, 530 and 930 without
+// the loads ahead.
+// FP32: on small grids (less than 4 workgroups a CU of the large form) the same,
+// one segment per workgroup: 10 steps at 80 x 81 x 50 30 us against 60, 128^3 54
+// against 66.  5 to 8 steps: segments of 4 levels, loads ahead, runs of 4 with the
+// level below carried: 256^3, 5 steps 262 us against 278, 1024 x 1024 x 512 8.47 ms
+// against 8.57.  Fewer or more steps: segments of 8 levels, runs of 2, loads of
+// the step itself (3 steps at 1024 x 1024 x 512 6.7 ms against 7.1, 10 steps 14.0
+// against 15.7, where the carry beside the loads ahead spills).
+template <typename T, int KM>
+void launch_grad_seg(mr_ctx* c, const GradArgs<T>& a, hipStream_t s) {
+  if constexpr (sizeof(T) == 8) {
+    launch_grad_form<T, KM, 4, false, true>(c, a, 1, s);
+  } else {
+    const int64_t wgs = (int64_t)((c->nx + kWave - 1) / kWave) * ((c->ny + kGradRows - 1) / kGradRows) *
+                        ((c->nz + 8 * kGradRun - 1) / (8 * kGradRun));
+    if (wgs < 4 * 256) launch_grad_form<T, KM, 4, false, true>(c, a, 1, s);
+    else if constexpr (KM == 8) launch_grad_form<T, KM, 4, true, true>(c, a, 4, s);
+    else launch_grad_form<T, KM, 8, true, false>(c, a, kGradRun, s);
+  }
 }
 
 template <typename T>
