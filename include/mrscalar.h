@@ -234,9 +234,9 @@ int mr_adjoint_seed(mr_ctx* ctx, int64_t n, const void* lam, void* mu_out, void*
  * n == 0: out = dL/dtheta^0 = lam^0 + tau_0 kappa Lh^T mu^0 (the start-up step
  *         reads theta^0 for its diffusion too).
  * out must not alias the inputs.  Velocity gradients are accumulated
- * separately by mr_velocity_grad.  Where mr_scalar_step is one streaming kernel,
- * so is the reverse step with n >= 1 and no lam_add.  Otherwise, on columns
- * taller than the line solver's
+ * separately by mr_velocity_grad.  Where the plain mr_scalar_step is one
+ * streaming kernel, so is the reverse step without lam_add.  Otherwise, on
+ * columns taller than the line solver's
  * the step runs as a column sweep (n >= 1: a sweep and a back substitution;
  * n = 0: one pass with no solve); lam_add is then refused (MR_ESHAPE). */
 int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const void* mu_cur,
@@ -251,8 +251,8 @@ int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const v
  * Every output must differ from the two levels before it (outs[0] from
  * mu_cur and mu_next, outs[1] from outs[0] and mu_cur, outs[q] from outs[q-1]
  * and outs[q-2]).  Results equal count calls of mr_scalar_step_backward to
- * rounding.  Where mr_scalar_step is one streaming kernel, so is each reverse
- * step here.  Otherwise, where the context runs step sequences as column sweeps
+ * rounding.  Where the plain mr_scalar_step is one streaming kernel, so is each
+ * reverse step here.  Otherwise, where the context runs step sequences as column sweeps
  * (mr_get_step_method 2) the reverse steps run as column sweeps too: each
  * kernel back-substitutes the previous reverse step's transposed solve while
  * it eliminates its own the other way (7 values per cell and step), with the

@@ -373,7 +373,7 @@ void launch_grad_form(mr_ctx* c, const GradArgs<T>& a, int most, hipStream_t s) 
 
 // FP64: segments of 4 levels, the next step's loads ahead, no carry (its
 // registers would not fit beside the accumulators at 4 wavefronts per SIMD):
-// 256^3, 3, 5 and 10 steps 358, 494 and 834 us against 380, 530 and 930 without
+// 256^3, 3, 5 and 10 steps 357, 495 and 835 us against 380, 540 and 935 without
 // the loads ahead.
 // FP32: on small grids (less than 4 workgroups a CU of the large form) the same,
 // one segment per workgroup: 10 steps at 80 x 81 x 50 30 us against 60, 128^3 54

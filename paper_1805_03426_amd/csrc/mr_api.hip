@@ -416,8 +416,9 @@ StreamHost stream_walk(const SweepHost& h, bool down) {
 }
 
 template <typename T>
-vector<mr::StreamRow<T>> stream_rows(const Axis& z, const SweepHost& h, const StreamHost& walk, bool rev, bool down) {
-  const int nz = z.n;
+vector<mr::StreamRow<T>> stream_rows(const vector<double>& ihz, const SweepHost& h, const StreamHost& walk, bool rev,
+                                     bool down) {
+  const int nz = (int)ihz.size();
   vector<mr::StreamRow<T>> r((size_t)nz + 2 * mr::kStreamRowPad);
   memset((void*)r.data(), 0, r.size() * sizeof(r[0]));
   for (int s = 0; s < nz; ++s) {
@@ -427,7 +428,7 @@ vector<mr::StreamRow<T>> stream_rows(const Axis& z, const SweepHost& h, const St
     o.ea = walk.a[s];
     o.tkb = h.tkb[k];
     // 1/hz of this level, of the one below and of the one above (0: a wall)
-    const double ih = 1.0 / z.h[k], ihl = k > 0 ? 1.0 / z.h[k - 1] : 0.0, ihh = k < nz - 1 ? 1.0 / z.h[k + 1] : 0.0;
+    const double ih = ihz[k], ihl = k > 0 ? ihz[k - 1] : 0.0, ihh = k < nz - 1 ? ihz[k + 1] : 0.0;
     const double lo = k > 0 ? ih : 0.0, hi = k < nz - 1 ? ih : 0.0;
     if (rev) {
       o.c0 = (T)(down ? -ihl : ihh);
@@ -815,6 +816,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   const bool streamv = !P.sweep_ok && desc->step_method == 0 && nch > 0 && uniform_axis(P.x) && uniform_axis(P.y) &&
                        ((int64_t)P.x.n * P.y.n * nz >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));
   size_t vro[mr::NKINDS], vcbo[mr::NKINDS];
+  const vector<double> ihz = inv(P.z.h);
   size_t sro[2][2][mr::NKINDS], scbo[2][2][mr::NKINDS];   // streaming tables: [transposed][down][kind]
   const double eps = f64 ? mr::kTruncate64 : mr::kTruncate32;
   int ahead = 0;                                      // the streaming step's look-ahead
@@ -826,11 +828,13 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     reach(nz, [&](int k) { return w.a[nz - 1 - k]; }, eps, [&](int k) -> int& { return before[d][nz - 1 - k]; });
     ahead = std::max(ahead, *std::max_element(after[d].begin(), after[d].end()));
   };
+  // (one allocation for the streaming tables: 13 sets of rows and back factors)
+  if (streams) pk.buf.reserve(pk.buf.size() + 16 * (size_t)(nz + 2 * mr::kStreamPad) * (sizeof(mr::StreamRow<double>) + 64));
   auto pack_stream = [&](const SweepHost& h, int kind, bool rev) {
     if (!streams) return;
     for (int d = 0; d < 2; ++d) {
       const StreamHost w = stream_walk(h, d);
-      sro[rev][d][kind] = f64 ? pk.put(stream_rows<double>(P.z, h, w, rev, d)) : pk.put(stream_rows<float>(P.z, h, w, rev, d));
+      sro[rev][d][kind] = f64 ? pk.put(stream_rows<double>(ihz, h, w, rev, d)) : pk.put(stream_rows<float>(ihz, h, w, rev, d));
       scbo[rev][d][kind] = pk.put(stream_cb(w));
       add_reach(w, d);
     }
@@ -884,7 +888,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   size_t o_sid = 0, o_sidcb = 0;
   if (streams) {
     const StreamHost w = stream_walk(shid, false);
-    o_sid = f64 ? pk.put(stream_rows<double>(P.z, shid, w, true, false)) : pk.put(stream_rows<float>(P.z, shid, w, true, false));
+    o_sid = f64 ? pk.put(stream_rows<double>(ihz, shid, w, true, false)) : pk.put(stream_rows<float>(ihz, shid, w, true, false));
     o_sidcb = pk.put(stream_cb(w));
   }
   // the streaming step's look-ahead, tiles and z segments
@@ -953,7 +957,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     c->swt[k] = sweep_ptrs(base, swto[k]);
   }
   c->swid = sweep_ptrs(base, swido);
-  // step sequences run as column sweeps where the line solver cannot take the
+  // where nothing streams, step sequences run as column sweeps where the line solver cannot take the
   // columns, and where the sweep's tiles keep the GPU full: at least 16
   // wavefronts per CU in all, and either one round of tiles (one workgroup
   // per CU: the sweep kernels run 4 wavefronts per SIMD) or rounds at least
