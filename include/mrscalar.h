@@ -181,8 +181,8 @@ int mr_divergence(mr_ctx* ctx, const void* u, const void* v, const void* w,
  * th_cur: callers rotate three buffers.  The tridiagonal elimination runs in
  * double for both precisions.  With step_method 0, x and y periodic with
  * uniform widths and the plain method, the step is one streaming kernel where
- * that is the fastest form (FP64 with an even N_x beyond one round of short
- * columns, or 4.5e6 cells and more, or columns taller than 640 levels) and the z system allows it: it back-
+ * that is the fastest form (all but small grids: mr_init's rule on precision,
+ * N_x, levels and cells) and the z system allows it: it back-
  * substitutes over a limited look-ahead, at most 60 levels, past which the
  * values left out enter the solution with a share below 7e-18 (FP64) or 1e-14
  * (FP32), less than the rounding of the stored type.  (A column that holds a

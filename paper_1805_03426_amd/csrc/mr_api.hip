@@ -796,12 +796,17 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   // 54 us against 30, 175^3 86 against 99; FP64 columns of at most 64 levels in
   // one round of tiles: 64^3 14.8 us against 13.3, 128 x 128 x 64 19.7 against
   // 16.1 (but 128^3 27.0 against 26.2, 160 x 160 x 64 21.5 against 24.4, 60 x 60
-  // x 128 18.4 against 24.4); FP32: 128^3 24 us against 16, 160^3 36 against 31,
-  // 176^3 41 against 51
+  // x 128 18.4 against 24.4); FP32 columns of at most 128 levels in one round:
+  // 128^3 17.9 against 16.1 (but 64 x 64 x 150 16.8 against 18.4, 64 x 64 x 500
+  // 26.4 against 36.5, 128 x 128 x 256 27.4 against 26.7, reverse 26.8 against
+  // 28.8), and FP32 grids of several rounds below 2.5e6 cells (150^3 31.3 against
+  // 36.4, 200 x 200 x 100 28.2 against 48.5)
   const bool one_round = ltiles <= cus;
+  const int64_t cells = (int64_t)P.x.n * P.y.n * nz;
   const bool streams = P.sweep_ok && desc->step_method == 0 &&
-                       (nch == 0 || (int64_t)P.x.n * P.y.n * nz >= 4500000 ||
-                        (f64 && P.x.n % 2 == 0 && !(one_round && nz <= 64)));
+                       (nch == 0 || cells >= 4500000 ||
+                        (f64 ? P.x.n % 2 == 0 && !(one_round && nz <= 64)
+                             : (one_round ? nz > 128 : cells >= 2500000)));
   // the variants' forward step streams (x and y of uniform widths) on grids of
   // 2.5e6 cells and more (FP64 with 4-byte copies 4.5e6) and on tall columns in
   // one round of tiles.  One step in us, line solver against streaming, with walls,
@@ -814,7 +819,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   // and 45
   const bool copies4 = f64 && P.x.n % 2 != 0;
   const bool streamv = !P.sweep_ok && desc->step_method == 0 && nch > 0 && uniform_axis(P.x) && uniform_axis(P.y) &&
-                       ((int64_t)P.x.n * P.y.n * nz >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));
+                       (cells >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));
   size_t vro[mr::NKINDS], vcbo[mr::NKINDS];
   const vector<double> ihz = inv(P.z.h);
   size_t sro[2][2][mr::NKINDS], scbo[2][2][mr::NKINDS];   // streaming tables: [transposed][down][kind]

@@ -67,3 +67,10 @@ def test_streaming_on_wide_grids_of_few_levels(nx, ny, nz, r):
     look-aheads longer than the column."""
     S.test_stream_steps_fp64(nx, ny, nz, r)
     S.test_stream_reverse_steps_fp64(nx, ny, nz, r)
+
+
+@pytest.mark.parametrize("nx,ny,nz,r", [(64, 20, 130, 0.3), (63, 9, 300, 0.05), (5, 3, 640, 0.9), (180, 170, 90, 0.05)])
+def test_streaming_fp32_on_tall_and_middle_grids(nx, ny, nz, r):
+    """FP32 columns of more than 128 levels in one round of tiles, and several
+    rounds below 4.5e6 cells."""
+    S.test_stream_fp32_matches_line_solver_and_sweeps(nx, ny, nz, r, "line")
