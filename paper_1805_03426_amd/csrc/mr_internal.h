@@ -318,13 +318,19 @@ __device__ __forceinline__ DD wave_sum(DD v) {
   return v;
 }
 
-// V consecutive values from p (one load; p needs its element's alignment only).
+// V consecutive values from p, and no byte past them (p needs its element's
+// alignment only).  One load, but three values as two and one: a vector type of
+// three holds four, and the compiler reads the fourth (three doubles as 32 bytes).
 template <typename T, int V>
-__device__ __forceinline__ void load_vec(const T* p, T* o) {
+__host__ __device__ __forceinline__ void load_vec(const T* p, T* o) {
   if constexpr (V == 1) {
     o[0] = *p;
+  } else if constexpr (V == 3) {
+    load_vec<T, 2>(p, o);
+    o[2] = p[2];
   } else {
     typedef T vt __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+    static_assert(sizeof(vt) == V * sizeof(T), "a vector type that holds V values and no more");
     const vt x = *reinterpret_cast<const vt*>(p);
 #pragma unroll
     for (int q = 0; q < V; ++q) o[q] = x[q];
