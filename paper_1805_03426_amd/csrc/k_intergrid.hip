@@ -96,10 +96,12 @@ void launch_integrate_t(mr_ctx* c, const T* th, T* tc, hipStream_t s) {
 // below (both mostly from the cache) and accumulates the faces on the low side
 // of its cells (plus the top plate for the last level).  At a ragged row end the
 // last lanes move back to the row's last V cells; those counted by the lane
-// before weigh nothing.  kDissAhead levels are loaded together and their faces
-// summed in double (positive terms: relative error at most kDissAhead + V eps)
-// before they enter the double-double sums.  Fixed partition: part[b] holds the
-// three double-double sums of the workgroup of logical index b; consecutive
+// before weigh nothing.  kDissAhead levels are loaded together; each column's
+// faces of those levels are summed in double (a term is a difference, its square
+// and a product with the width, each rounded once, then kDissAhead - 1 positive
+// sums and the column's weight: relative error at most kDissAhead + 5 eps) and
+// enter the double-double sums column by column.  Fixed partition: part[b] holds
+// the three double-double sums of the workgroup of logical index b; consecutive
 // tiles run on one XCD.
 constexpr int kDissMaxParts = 2048;
 constexpr int kDissAhead = 4;
@@ -185,16 +187,12 @@ __global__ void __launch_bounds__(64 * kDissRows) diss_partial(const T* th, cons
         below[q] = v;
       }
     }
-    double bx_ = 0.0, by_ = 0.0, bz_ = 0.0;
 #pragma unroll
     for (int q = 0; q < V; ++q) {
-      bx_ += ax[q] * wx[q];
-      by_ += ay[q] * wy[q];
-      bz_ += az[q] * area[q];
+      sx = dd_add(sx, ax[q] * wx[q]);
+      sy = dd_add(sy, ay[q] * wy[q]);
+      sz = dd_add(sz, az[q] * area[q]);
     }
-    sx = dd_add(sx, bx_);
-    sy = dd_add(sy, by_);
-    sz = dd_add(sz, bz_);
   }
   sx = wave_sum(sx);
   sy = wave_sum(sy);
