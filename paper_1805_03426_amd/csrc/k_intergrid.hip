@@ -264,9 +264,13 @@ hipError_t launch_integrate(mr_ctx* c, const void* th, void* tc, hipStream_t s) 
 }
 
 hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_t s) {
-  // V cells a lane: 16 bytes of them, one where a row is shorter than that
-  const bool f64 = c->precision == MR_FP64, vec = c->nx >= (f64 ? 2 : 4);
-  const int V = vec ? (f64 ? 2 : 4) : 1;
+  // cells a lane: two in FP64, one in FP32 and on rows of one cell.  In us, 8e6
+  // cells: FP32 with one, two and four 450 x 177 x 100 22.5, 23.3, 25.4; 256 x 312 x
+  // 100 22.0, 21.3, 22.6; 40 x 2000 x 100 25.6, 35.1, 55.4 (four leave most lanes of
+  // a short row idle); 8 x 10000 x 100 72, 108, 205; FP64 with one and two 450 x 177
+  // x 100 26.2, 25.1; 256 x 312 x 100 26.1, 23.5; 40 x 2000 x 100 31.5, 36.3
+  const bool f64 = c->precision == MR_FP64, vec = f64 && c->nx >= 2;
+  const int V = vec ? 2 : 1;
   const int nbx = (c->nx + kWave * V - 1) / (kWave * V), nby = (c->ny + kDissRows - 1) / kDissRows;
   const int64_t tiles = (int64_t)nbx * nby;
   // level ranges: about kDissWaves wavefronts in all (ranges as long as that
@@ -288,7 +292,7 @@ hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_
                        g.idyc, c->idcz, c->nx, c->ny, c->nz, nbx, nby, kb, c->wx, c->wy, db, dtp, c->t_bot, c->t_top,
                        c->red);
   } else {
-    auto k = vec ? diss_partial<float, 4> : diss_partial<float, 1>;
+    auto k = diss_partial<float, 1>;
     hipLaunchKernelGGL(k, dim3((unsigned)nb), block, 0, s, (const float*)th, c->hx64, c->areaw, c->hz64, g.idxc,
                        g.idyc, c->idcz, c->nx, c->ny, c->nz, nbx, nby, kb, c->wx, c->wy, db, dtp, c->t_bot, c->t_top,
                        c->red);
