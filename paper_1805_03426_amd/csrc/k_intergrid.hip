@@ -4,9 +4,10 @@
 // with eps_T = kappa <|grad theta|^2>_V (Sec. 4.1, Eq. 23).
 //
 // Integration: one lane per coarse cell, 256 consecutive ones (x fastest) a
-// workgroup.  A lane reads its mx values of each of the my x mz dense rows with
-// one load (mx <= 4), all of them independent, and sums in double: the columns
-// over the rows first, then across x.  The dense field is read once.
+// workgroup.  A lane reads its mx values of each of the my x mz dense rows at
+// once (mx <= 4; larger factors: integrate_columns), all of them independent, and
+// sums in double: the columns over the rows first, then across x.  The dense
+// field is read once.
 //
 // Dissipation: every dense cell owns its low x face, low y face and low z face
 // (and the top plate for the last level); each face adds its squared
@@ -22,72 +23,140 @@ namespace {
 
 constexpr int kIntBlock = 256;
 
-// MX, MY, MZ: the refinement factors, 0 for any (then from the arguments).
+// MX <= 4, MY, MZ: the refinement factors, MY and MZ 0 for any (then from the arguments).
 template <typename T, int MX, int MY, int MZ>
 __global__ void __launch_bounds__(kIntBlock) integrate_kernel(const T* th, T* tc, const double* hx,
                                                               const double* hy, const double* hz,
-                                                              int nx, int ny, int mx_, int my_, int mz_,
+                                                              int nx, int ny, int my_, int mz_,
                                                               int ncx, int ncy, int cells) {
   const int c = xcd_remap(blockIdx.x, gridDim.x) * kIntBlock + threadIdx.x;
   if (c >= cells) return;
   const int my = MY ? MY : my_, mz = MZ ? MZ : mz_;
   const int KJ = c / ncx, I = c - KJ * ncx, K = KJ / ncy, J = KJ - K * ncy;
   const size_t nxy = (size_t)nx * ny;
-  if constexpr (MX > 0) {
-    double acc[MX], vyz = 0.0;
+  double acc[MX], vyz = 0.0;
 #pragma unroll
-    for (int q = 0; q < MX; ++q) acc[q] = 0.0;
-    for (int kk = 0; kk < mz; ++kk) {
+  for (int q = 0; q < MX; ++q) acc[q] = 0.0;
+  for (int kk = 0; kk < mz; ++kk) {
+    for (int jj = 0; jj < my; ++jj) {
+      T v[MX];
+      load_vec<T, MX>(th + (size_t)(K * mz + kk) * nxy + (size_t)(J * my + jj) * nx + I * MX, v);
+      const double wyz = hy[J * my + jj] * hz[K * mz + kk];
+#pragma unroll
+      for (int q = 0; q < MX; ++q) acc[q] += (double)v[q] * wyz;
+      vyz += wyz;
+    }
+  }
+  double num = 0.0, hxs = 0.0;
+#pragma unroll
+  for (int q = 0; q < MX; ++q) {
+    const double w = hx[I * MX + q];
+    num += acc[q] * w;
+    hxs += w;
+  }
+  tc[c] = (T)(num / (hxs * vyz));
+}
+
+// M_x = 1 with several dense rows a coarse cell, on rows of coarse cells that
+// fill wavefronts: as above, but a wavefront stays in one coarse row, so that the
+// y and z widths are scalar loads (as vector loads they are as many again as the
+// field's).  FP64, 512 x 512 x 128, M = 1, 2, 2: 69 us, 80 without it; 256^3 26.5
+// and 29.2.
+template <typename T>
+__global__ void __launch_bounds__(kIntBlock) integrate_rows(const T* th, T* tc, const double* hx, const double* hy,
+                                                            const double* hz, int nx, int ny, int my, int mz, int ncy,
+                                                            int ntx, int tiles) {
+  const int tile = blockIdx.x * (kIntBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int row = tile / ntx, K = row / ncy, J = row - K * ncy;
+  const int I = (tile - row * ntx) * kWave + threadIdx.x % kWave;
+  if (tile >= tiles || I >= nx) return;
+  const size_t nxy = (size_t)nx * ny;
+  const T* const p = th + (size_t)K * mz * nxy + (size_t)J * my * nx + I;
+  const double *const py = hy + J * my, *const pz = hz + K * mz;
+  double acc = 0.0, vyz = 0.0;
+  for (int kk = 0; kk < mz; ++kk)
+    for (int jj = 0; jj < my; ++jj) {
+      const double wyz = py[jj] * pz[kk];
+      acc += (double)p[(size_t)kk * nxy + (size_t)jj * nx] * wyz;
+      vyz += wyz;
+    }
+  const double w = hx[I];
+  tc[(size_t)row * nx + I] = (T)(acc * w / (w * vyz));
+}
+
+// M_x from 5 to kIntBlock: a lane per dense column of a coarse cell,
+// floor(kIntBlock / mx) consecutive coarse cells (x fastest) a workgroup.  A lane
+// sums its column over the cell's dense rows, so that the lanes read rows of the
+// field side by side (a lane per coarse cell reads every line mx times: 256^3
+// FP64, M = 16, 2, 2 317 us, here 29; M = 5, 2, 2 89 and 28); the cell's first
+// lane adds the columns up in order.  U: dense rows whose loads go out together
+// (4 from M_y = 4 on: M = 8, 8, 8 22 us, 30 with 1; M = 5, 2, 2 30 with 4).
+template <typename T, int U>
+__global__ void __launch_bounds__(kIntBlock) integrate_columns(const T* th, T* tc, const double* hx,
+                                                               const double* hy, const double* hz, int nx, int ny,
+                                                               int mx, int my, int mz, int ncx, int ncy, int cells) {
+  __shared__ double s_acc[kIntBlock];
+  __shared__ double s_hx[kIntBlock];
+  const int t = threadIdx.x, cell = t / mx, sub = t - cell * mx, per = kIntBlock / mx;
+  const int c = xcd_remap(blockIdx.x, gridDim.x) * per + cell;
+  const bool on = cell < per && c < cells;
+  double acc = 0.0, vyz = 0.0, wx = 0.0;
+  if (on) {
+    const int KJ = c / ncx, I = c - KJ * ncx, K = KJ / ncy, J = KJ - K * ncy;
+    const T* p = th + ((size_t)K * mz * ny + (size_t)J * my) * nx + I * mx + sub;
+    const size_t nxy = (size_t)nx * ny;
+    wx = hx[I * mx + sub];
+    for (int kk = 0; kk < mz; ++kk)
+#pragma unroll U
       for (int jj = 0; jj < my; ++jj) {
-        T v[MX];
-        load_vec<T, MX>(th + (size_t)(K * mz + kk) * nxy + (size_t)(J * my + jj) * nx + I * MX, v);
         const double wyz = hy[J * my + jj] * hz[K * mz + kk];
-#pragma unroll
-        for (int q = 0; q < MX; ++q) acc[q] += (double)v[q] * wyz;
+        acc += (double)p[kk * nxy + (size_t)jj * nx] * wyz;
         vyz += wyz;
       }
-    }
+  }
+  s_acc[t] = acc * wx;
+  s_hx[t] = wx;
+  __syncthreads();
+  if (on && sub == 0) {
     double num = 0.0, hxs = 0.0;
-#pragma unroll
-    for (int q = 0; q < MX; ++q) {
-      const double w = hx[I * MX + q];
-      num += acc[q] * w;
-      hxs += w;
-    }
-    tc[c] = (T)(num / (hxs * vyz));
-  } else {
-    double num = 0.0, hxs = 0.0, vyz = 0.0;
-    for (int q = 0; q < mx_; ++q) {
-      double acc = 0.0;
-      vyz = 0.0;
-      for (int kk = 0; kk < mz; ++kk)
-        for (int jj = 0; jj < my; ++jj) {
-          const double wyz = hy[J * my + jj] * hz[K * mz + kk];
-          acc += (double)th[(size_t)(K * mz + kk) * nxy + (size_t)(J * my + jj) * nx + I * mx_ + q] * wyz;
-          vyz += wyz;
-        }
-      const double w = hx[I * mx_ + q];
-      num += acc * w;
-      hxs += w;
+    for (int q = 0; q < mx; ++q) {
+      num += s_acc[t + q];
+      hxs += s_hx[t + q];
     }
     tc[c] = (T)(num / (hxs * vyz));
   }
 }
 
 template <typename T>
-void launch_integrate_t(mr_ctx* c, const T* th, T* tc, hipStream_t s) {
+hipError_t launch_integrate_t(mr_ctx* c, const T* th, T* tc, hipStream_t s) {
   const int cells = c->ncx * c->ncy * c->ncz;
-  const dim3 grid((unsigned)((cells + kIntBlock - 1) / kIntBlock)), block(kIntBlock);
+  const dim3 block(kIntBlock);
+  if (c->mx > 4) {
+    const int per = kIntBlock / c->mx;
+    if (per < 1) return hipErrorInvalidValue;
+    auto k = c->my >= 4 ? integrate_columns<T, 4> : integrate_columns<T, 1>;
+    hipLaunchKernelGGL(k, dim3((unsigned)((cells + per - 1) / per)), block, 0, s, th, tc, c->hx64, c->areaw, c->hz64,
+                       c->nx, c->ny, c->mx, c->my, c->mz, c->ncx, c->ncy, cells);
+    return hipGetLastError();
+  }
+  const int ntx = (c->ncx + kWave - 1) / kWave;
+  if (c->mx == 1 && c->my * c->mz > 1 && 5 * c->ncx >= 4 * ntx * kWave) {   // (at least 4/5 of the lanes in use)
+    const int tiles = ntx * c->ncy * c->ncz, waves = kIntBlock / kWave;
+    hipLaunchKernelGGL(integrate_rows<T>, dim3((unsigned)((tiles + waves - 1) / waves)), block, 0, s, th, tc, c->hx64,
+                       c->areaw, c->hz64, c->nx, c->ny, c->my, c->mz, c->ncy, ntx, tiles);
+    return hipGetLastError();
+  }
+  const dim3 grid((unsigned)((cells + kIntBlock - 1) / kIntBlock));
   // the equal factors 2 and 3 unrolled whole (their loads go out together)
-  auto k = integrate_kernel<T, 0, 0, 0>;
+  auto k = integrate_kernel<T, 1, 0, 0>;
   if (c->mx == 2 && c->my == 2 && c->mz == 2) k = integrate_kernel<T, 2, 2, 2>;
   else if (c->mx == 3 && c->my == 3 && c->mz == 3) k = integrate_kernel<T, 3, 3, 3>;
-  else if (c->mx == 1) k = integrate_kernel<T, 1, 0, 0>;
   else if (c->mx == 2) k = integrate_kernel<T, 2, 0, 0>;
   else if (c->mx == 3) k = integrate_kernel<T, 3, 0, 0>;
   else if (c->mx == 4) k = integrate_kernel<T, 4, 0, 0>;
-  hipLaunchKernelGGL(k, grid, block, 0, s, th, tc, c->hx64, c->areaw, c->hz64, c->nx, c->ny, c->mx, c->my, c->mz,
-                     c->ncx, c->ncy, cells);
+  hipLaunchKernelGGL(k, grid, block, 0, s, th, tc, c->hx64, c->areaw, c->hz64, c->nx, c->ny, c->my, c->mz, c->ncx,
+                     c->ncy, cells);
+  return hipGetLastError();
 }
 
 // Nu_T partials: a workgroup of kDissRows wavefronts covers kDissRows rows of
@@ -258,9 +327,8 @@ __global__ void __launch_bounds__(kDissFinal) diss_final(const double* part, int
 }  // namespace
 
 hipError_t launch_integrate(mr_ctx* c, const void* th, void* tc, hipStream_t s) {
-  if (c->precision == MR_FP64) launch_integrate_t<double>(c, (const double*)th, (double*)tc, s);
-  else launch_integrate_t<float>(c, (const float*)th, (float*)tc, s);
-  return hipGetLastError();
+  return c->precision == MR_FP64 ? launch_integrate_t<double>(c, (const double*)th, (double*)tc, s)
+                                 : launch_integrate_t<float>(c, (const float*)th, (float*)tc, s);
 }
 
 hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_t s) {
