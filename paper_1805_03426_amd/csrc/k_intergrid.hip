@@ -331,31 +331,49 @@ hipError_t launch_integrate(mr_ctx* c, const void* th, void* tc, hipStream_t s) 
                                  : launch_integrate_t<float>(c, (const float*)th, (float*)tc, s);
 }
 
-hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_t s) {
+namespace {
+
+struct DissGrid {
+  int V, nbx, nby, kb;
+  int64_t nb;
+};
+DissGrid diss_grid(const mr_ctx* c) {
+  DissGrid g;
   // cells a lane: two in FP64, one in FP32 and on rows of one cell.  In us, 8e6
   // cells: FP32 with one, two and four 450 x 177 x 100 22.5, 23.3, 25.4; 256 x 312 x
   // 100 22.0, 21.3, 22.6; 40 x 2000 x 100 25.6, 35.1, 55.4 (four leave most lanes of
   // a short row idle); 8 x 10000 x 100 72, 108, 205; FP64 with one and two 450 x 177
   // x 100 26.2, 25.1; 256 x 312 x 100 26.1, 23.5; 40 x 2000 x 100 31.5, 36.3
-  const bool f64 = c->precision == MR_FP64, vec = f64 && c->nx >= 2;
-  const int V = vec ? 2 : 1;
-  const int nbx = (c->nx + kWave * V - 1) / (kWave * V), nby = (c->ny + kDissRows - 1) / kDissRows;
-  const int64_t tiles = (int64_t)nbx * nby;
+  g.V = c->precision == MR_FP64 && c->nx >= 2 ? 2 : 1;
+  g.nbx = (c->nx + kWave * g.V - 1) / (kWave * g.V);
+  g.nby = (c->ny + kDissRows - 1) / kDissRows;
+  const int64_t tiles = (int64_t)g.nbx * g.nby;
   // level ranges: about kDissWaves wavefronts in all (ranges as long as that
   // allows: each workgroup ends with a reduction), at most kDissMaxParts partials
   const int64_t want = (kDissWaves / kDissRows + tiles - 1) / tiles;
-  int nkb = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)c->nz, want, kDissMaxParts / tiles}));
-  const int kb = (c->nz + nkb - 1) / nkb;
-  nkb = (c->nz + kb - 1) / kb;
-  const int64_t nb = tiles * nkb;
-  if (nb > INT32_MAX) return hipErrorInvalidValue;
-  hipError_t e = ensure_red(c, sizeof(double) * 6 * (size_t)nb);
+  const int nkb = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)c->nz, want, kDissMaxParts / tiles}));
+  g.kb = (c->nz + nkb - 1) / nkb;
+  g.nb = tiles * ((c->nz + g.kb - 1) / g.kb);
+  return g;
+}
+
+}  // namespace
+
+size_t diss_bytes(const mr_ctx* c) { return sizeof(double) * 6 * (size_t)diss_grid(c).nb; }
+
+hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_t s) {
+  const bool f64 = c->precision == MR_FP64;
+  const DissGrid d = diss_grid(c);
+  if (d.nb > INT32_MAX) return hipErrorInvalidValue;
+  const int nbx = d.nbx, nby = d.nby, kb = d.kb;
+  const int64_t nb = d.nb;
+  const hipError_t e = ensure_red(c);
   if (e != hipSuccess) return e;
   const int db = c->bc_bot == MR_DIRICHLET, dtp = c->bc_top == MR_DIRICHLET;
   const Geom<double>& g = c->g64;
   const dim3 block(kWave, kDissRows);
   if (f64) {
-    auto k = vec ? diss_partial<double, 2> : diss_partial<double, 1>;
+    auto k = d.V == 2 ? diss_partial<double, 2> : diss_partial<double, 1>;
     hipLaunchKernelGGL(k, dim3((unsigned)nb), block, 0, s, (const double*)th, c->hx64, c->areaw, c->hz64, g.idxc,
                        g.idyc, c->idcz, c->nx, c->ny, c->nz, nbx, nby, kb, c->wx, c->wy, db, dtp, c->t_bot, c->t_top,
                        c->red);

@@ -396,29 +396,51 @@ void nusselt_kernels(mr_ctx* c, const void* th, const void* w, double* prof, dou
 
 }  // namespace
 
-hipError_t ensure_red(mr_ctx* c, size_t bytes) {
-  if (c->red_bytes >= bytes) return hipSuccess;
-  if (c->red) (void)hipFree(c->red);
-  c->red = nullptr;
-  c->red_bytes = 0;
-  hipError_t e = hipMalloc((void**)&c->red, bytes);
-  if (e == hipSuccess) c->red_bytes = bytes;
+namespace {
+
+// The divergence's launch: level ranges for about kDivWaves wavefronts in all, 8 levels at least.
+struct DivGrid {
+  int V, nbx, nby, kb;
+  int64_t nb;
+};
+DivGrid div_grid(const mr_ctx* c) {
+  DivGrid g;
+  g.V = wide_rows(c) ? (c->precision == MR_FP64 ? 2 : 4) : 1;
+  g.nbx = (c->nx + kWave * g.V - 1) / (kWave * g.V);
+  g.nby = (c->ny + kDivRows - 1) / kDivRows;
+  const int64_t tiles = (int64_t)g.nbx * g.nby;
+  const int nkb = (int)std::max<int64_t>(1, std::min<int64_t>((kDivWaves / kDivRows + tiles - 1) / tiles, c->nz / 8));
+  g.kb = (c->nz + nkb - 1) / nkb;
+  g.nb = tiles * ((c->nz + g.kb - 1) / g.kb);
+  return g;
+}
+
+size_t nu_bytes(const mr_ctx* c) {
+  return c->nz > kNuMaxFaces ? 0 : sizeof(double) * 4 * (size_t)c->nz * nu_parts(c);
+}
+
+}  // namespace
+
+// One buffer for the partials of all three reductions, as large as the largest
+// needs: whichever is called first allocates it, and it is neither moved nor
+// freed before the context is, so a captured call keeps a valid address whatever
+// is called after it.
+hipError_t ensure_red(mr_ctx* c) {
+  if (c->red) return hipSuccess;
+  const size_t bytes = std::max({sizeof(double) * 2 * (size_t)div_grid(c).nb, nu_bytes(c), diss_bytes(c)});
+  const hipError_t e = hipMalloc((void**)&c->red, bytes);
+  if (e != hipSuccess) c->red = nullptr;
   return e;
 }
 
-// Level ranges for about kDivWaves wavefronts in all, 8 levels at least.
 hipError_t launch_divergence(mr_ctx* c, const void* u, const void* v, const void* w, double* out,
                              hipStream_t s) {
   const bool f64 = c->precision == MR_FP64, vec = wide_rows(c);
-  const int V = vec ? (f64 ? 2 : 4) : 1;
-  const int nbx = (c->nx + kWave * V - 1) / (kWave * V), nby = (c->ny + kDivRows - 1) / kDivRows;
-  const int64_t tiles = (int64_t)nbx * nby;
-  int nkb = (int)std::max<int64_t>(1, std::min<int64_t>((kDivWaves / kDivRows + tiles - 1) / tiles, c->nz / 8));
-  const int kb = (c->nz + nkb - 1) / nkb;
-  nkb = (c->nz + kb - 1) / kb;
-  const int64_t nb = tiles * nkb;
-  if (nb > INT32_MAX) return hipErrorInvalidValue;
-  hipError_t e = ensure_red(c, sizeof(double) * 2 * (size_t)nb);
+  const DivGrid g = div_grid(c);
+  if (g.nb > INT32_MAX) return hipErrorInvalidValue;
+  const int nbx = g.nbx, nby = g.nby, kb = g.kb;
+  const int64_t nb = g.nb;
+  const hipError_t e = ensure_red(c);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)nb), block(kWave, kDivRows);
   if (f64) {
@@ -436,9 +458,8 @@ hipError_t launch_divergence(mr_ctx* c, const void* u, const void* v, const void
 
 hipError_t launch_nusselt(mr_ctx* c, const void* th, const void* w, double* prof, hipStream_t s) {
   const int P = nu_parts(c);
-  const size_t part = (size_t)c->nz * P * 4;
   if (c->nz > kNuMaxFaces) return hipErrorInvalidValue;
-  hipError_t e = ensure_red(c, sizeof(double) * part);
+  const hipError_t e = ensure_red(c);
   if (e != hipSuccess) return e;
   nusselt_kernels(c, th, w, prof, c->red, P, s);
   return hipGetLastError();

@@ -226,7 +226,6 @@ struct mr_ctx {
   void* interp_bwd_tmp;            // transposed refinement intermediates (lazy)
   size_t interp_bwd_tmp_bytes;
   double* red;                     // reduction partials
-  size_t red_bytes;
 };
 
 // Launchers (return hipError_t of the launch).
@@ -284,8 +283,9 @@ hipError_t launch_stream_step_var(mr_ctx* c, int64_t n, const void* thp, const v
                                   const void* v, const void* w, hipStream_t s);
 hipError_t launch_stream_step_backward(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* out,
                                        const void* u, const void* v, const void* w, hipStream_t s);
-// Grows the context's reduction scratch to at least `bytes`.
-hipError_t ensure_red(mr_ctx* c, size_t bytes);
+// Allocates the context's reduction scratch on the first call.
+hipError_t ensure_red(mr_ctx* c);
+size_t diss_bytes(const mr_ctx* c);   // what the dissipation's partials take of it
 // The fixed device memory of the allocation-free Nusselt entry point: looks up
 // its address on `device` (the current device) once per device.
 hipError_t scratch_init(int device);
