@@ -47,7 +47,7 @@ WORKLOAD = "rb1024x1024x512-m2-fp64"
 SMALL_WORKLOAD = "rb256-m2-fp64"
 ADJOINT_WORKLOAD = "rb256-m2-adjoint-fp32"
 CPU_WORKLOAD = "rb256-m2-fp64"
-STEP_KERNELS = {"line": "line_kernel", "stream": "stream_kernel"}
+STEP_KERNELS = {"line": "line_kernel", "sweep": "sweep_kernel", "stream": "stream_kernel"}
 # committed counter summaries of the step kernels, by workload
 PROFILE_TRAFFIC = {"rb1024x1024x512-m2-fp64": os.path.join(ROOT, "profiles", "scalar_step_rb1024x1024x512_fp64_traffic.md"),
                    "rb256-m2-fp64": os.path.join(ROOT, "profiles", "scalar_step_rb256_fp64_traffic.md")}
@@ -64,18 +64,12 @@ def workload_inputs(w):
     return _INPUTS[key]
 
 
-def step_form(w):
-    """The form in which the library runs the FP64 steps of a uniform periodic
-    workload: the line solver on one round of short columns, else streaming."""
-    nx, ny, nz = w.n
-    return "line" if nz <= 64 and -(-nx // 32) * -(-ny // 2) <= 256 else "stream"
-
-
 def kernel_source_hash(method="stream"):
     """Hash of the sources that define the step kernel of a method and its
     launch shape (the kernel code, its launch code and the shared header), to
     tell whether the committed counters of that kernel are stale."""
     names = {"stream": ("stream_kernel.h", "k_stream.hip", "mr_internal.h"),
+             "sweep": ("k_sweep.hip", "mr_internal.h"),
              "line": ("line_kernel.h", "k_line_fwd.hip", "k_step.hip", "mr_internal.h", "mr_api.hip")}[method]
     h = hashlib.sha256()
     for name in names:
@@ -339,7 +333,7 @@ def large_step_times():
         ms = sequence_ms(r)
         nbytes = 6 * (8 if prec == "fp64" else 4) * w.cells
         key = name if prec == "fp32" else name.replace("fp32", "fp64")
-        out[key] = dict(step_method=step_form(w), step_ms=ms, dense_cell_updates_per_s=w.cells / (ms * 1e-3),
+        out[key] = dict(step_method=c.step_form("scalar_steps"), step_ms=ms, dense_cell_updates_per_s=w.cells / (ms * 1e-3),
                         step_hbm_frac_alg=nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS)
         c.close()
         del r
@@ -355,7 +349,7 @@ def whole_runs(w, precision, k, warmup):
     el = time_runs(r, k, warmup, ev)
     ms = kernel_ms(ev)
     vb = 8 if precision == "fp64" else 4
-    out = dict(workload=w.name, precision=precision, step_method=step_form(w),
+    out = dict(workload=w.name, precision=precision, step_method=r.ctx.step_form("scalar_steps"),
                value=w.cells * w.steps * k / el,
                unit="dense-cell updates/s", ms_per_run=el / k * 1e3, step_kernel_ms=ms,
                step_hbm_frac_alg=6 * vb * w.cells / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS)
@@ -479,7 +473,7 @@ def main():
     w = WORKLOADS[args.workload]
     print("bench: %s, %d runs + %d warmup" % (w.name, args.steps, args.warmup), file=sys.stderr, flush=True)
     run = Run(w, "fp64")
-    form = step_form(w)
+    form = run.ctx.step_form("scalar_steps")
     step_kernel = STEP_KERNELS[form]
     events = []
     el = time_runs(run, args.steps, args.warmup, events)

@@ -393,8 +393,15 @@ int mr_host_face_weights(const mr_desc* desc, int32_t axis, double* w_out);
 
 /* The method mr_scalar_steps uses on this context: 1 = the fused line
  * solver, 2 = column sweeps.  With step_method 0 the streaming step may stand
- * in for either (see mr_scalar_step). */
+ * in for either: mr_get_step_form names what runs. */
 int mr_get_step_method(const mr_ctx* ctx, int32_t* method);
+
+/* The form in which a call runs its steps on this context: 1 = the fused line
+ * solver, 2 = column sweeps, 3 = the streaming step.  call: 0 = mr_scalar_step,
+ * 1 = mr_scalar_steps (and mr_coarse_step), 2 = mr_scalar_step_backward without
+ * lam_add, 3 = mr_scalar_steps_backward (1 there stands for the line solver's
+ * reverse steps one after the other).  MR_EINVAL for another call. */
+int mr_get_step_form(const mr_ctx* ctx, int32_t call, int32_t* form);
 
 /* Dense sizes of a context and its precision. */
 int mr_get_dims(const mr_ctx* ctx, int32_t* nx, int32_t* ny, int32_t* nz, int32_t* precision);

@@ -23,7 +23,7 @@ EXPORTS = [
     "mr_host_z_system", "mr_get_dims", "mr_status_string", "mr_last_hip_error",
     "mr_thermal_dissipation", "mr_interpolate_velocity_time", "mr_integrate_scalar",
     "mr_coarse_step", "mr_host_z_face_weights", "mr_host_face_weights", "mr_scalar_steps",
-    "mr_scalar_steps_backward", "mr_get_step_method",
+    "mr_scalar_steps_backward", "mr_get_step_method", "mr_get_step_form",
     "mr_nusselt_noalloc",
 ]
 
@@ -108,6 +108,7 @@ def lib():
         "mr_get_dims": (c_int, [P, POINTER(c_int32), POINTER(c_int32), POINTER(c_int32),
                                 POINTER(c_int32)]),
         "mr_get_step_method": (c_int, [P, POINTER(c_int32)]),
+        "mr_get_step_form": (c_int, [P, c_int32, POINTER(c_int32)]),
         "mr_status_string": (c_char_p, [c_int]),
         "mr_last_hip_error": (c_int, [P]),
     }

@@ -19,6 +19,7 @@ _BC = {"dirichlet": _lib.MR_DIRICHLET, "adiabatic": _lib.MR_ADIABATIC}
 _PREC = {"fp64": _lib.MR_FP64, "fp32": _lib.MR_FP32}
 _SIDE = {"periodic": _lib.MR_PERIODIC, "walls": _lib.MR_WALLS}
 _METHOD = {"auto": 0, "line": 1, "sweep": 2}
+_CALL = {"scalar_step": 0, "scalar_steps": 1, "scalar_step_backward": 2, "scalar_steps_backward": 3}
 
 
 def make_desc(xf, yf, zf, m, ra, pr, dt, n_avg=50, t_bot=1.0, t_top=0.0, bc_bot="dirichlet",
@@ -306,10 +307,20 @@ class Context:
 
     @property
     def step_method(self):
-        """The method step sequences run with: "line" or "sweep"."""
+        """The method step sequences run with where nothing streams: "line" or
+        "sweep" (``step_form`` names what runs)."""
         m = c_int32()
         check(lib().mr_get_step_method(self._ctx, byref(m)), "mr_get_step_method", self._ctx)
         return "sweep" if m.value == 2 else "line"
+
+    def step_form(self, call="scalar_step"):
+        """The form in which a call runs its steps here: "line" (the fused line
+        solver), "sweep" (column sweeps) or "stream" (the streaming step); call:
+        "scalar_step", "scalar_steps", "scalar_step_backward" (without lam_add)
+        or "scalar_steps_backward"."""
+        form = c_int32()
+        check(lib().mr_get_step_form(self._ctx, c_int32(_CALL[call]), byref(form)), "mr_get_step_form", self._ctx)
+        return ("line", "sweep", "stream")[form.value - 1]
 
     def step_runner(self, ring, u, v, w):
         """Prepared repeated stepping on fixed buffers: checks the buffers once

@@ -703,6 +703,15 @@ int mr_get_step_method(const mr_ctx* ctx, int32_t* method) {
   return MR_OK;
 }
 
+int mr_get_step_form(const mr_ctx* ctx, int32_t call, int32_t* form) {
+  if (!ctx || !form || call < 0 || call > 3) return MR_EINVAL;
+  const bool back = call >= 2, sequence = call & 1;
+  if (ctx->stream_d || (!back && ctx->stream_v)) *form = 3;
+  else if (sequence ? ctx->sweep_pref : back ? ctx->nch == 0 : ctx->sweep_single) *form = 2;
+  else *form = 1;
+  return MR_OK;
+}
+
 int mr_get_dims(const mr_ctx* ctx, int32_t* nx, int32_t* ny, int32_t* nz, int32_t* precision) {
   if (!ctx) return MR_EINVAL;
   if (nx) *nx = ctx->nx;
