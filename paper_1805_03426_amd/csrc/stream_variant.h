@@ -3,17 +3,22 @@
 // combination, on uniform x and y widths.  The walk, the look-ahead, the ring of
 // elimination values and the copies into LDS are those of the plain streaming
 // step (stream_kernel.h); what differs:
-//   - the right-hand side takes face values from four-cell weights on every axis
-//     (second order: 0, 1/2, 1/2, 0), so the advected field comes with a halo of
-//     two rows and at least two columns, and a level is closed by the field two
-//     levels ahead;
+//   - fourth order (ORD4): face values come from four-cell weights on every axis,
+//     so the advected field comes with a halo of two rows and at least two columns,
+//     and a level is closed by the field two levels ahead.  Second order reads the
+//     two cells beside a face only (four cells with weights 0, 1/2, 1/2, 0 let a
+//     value that is not finite in two cells further: 0 times it is not 0; 150^3
+//     with walls, look-ahead 16: FP64 56.6 us with them, 49.0 without, FP32 35.8 and
+//     34.0);
 //   - the explicit z share reads the lagged field one level each way, from the
 //     column's own values carried along the walk;
 //   - a wall's faces have zero weights and carry no velocity, and what the copies
-//     bring from beyond it is the chunk or row next to it;
+//     bring from beyond it is the chunk or row next to it: the cell itself or one
+//     that its other faces weigh, but for FP32 chunks of four columns, where the
+//     cell takes its own value instead;
 //   - the walk always goes up, and the weights hold registers: workgroups of at
 //     most 12 wavefronts.
-// One kernel serves all variants: products with zero weights cost it little.
+// Walls and the explicit z share are no template parameters: they cost little.
 // On grids that fill the GPU it is bound by the bytes (400 x 300 x 200 FP64: 294 us,
 // 3.9 TB/s of the 6 values per cell; the plain step 275), on small ones by a
 // level's chain from barrier to barrier (0.6 us with one wavefront per SIMD, 0.9
@@ -76,7 +81,7 @@ __device__ __forceinline__ int wrap_any(int i, int n) {
   return wrap(i, n);
 }
 
-template <typename T, int D, int TX, int TY, int CH>
+template <typename T, int D, int TX, int TY, int CH, bool ORD4>
 __global__ void __launch_bounds__(64 * TX * TY) stream_var_kernel(VarArgs<T> A) {
   constexpr int B = kStreamBlock;
   using L = VarTile<T, TX, TY, CH>;
@@ -145,10 +150,9 @@ __global__ void __launch_bounds__(64 * TX * TY) stream_var_kernel(VarArgs<T> A) 
   const bool walls = A.wx || A.wy;
   const bool xl = A.wx && i == 0, xh = A.wx && i == nx - 1, yl = A.wy && j == 0, yh = A.wy && j == ny - 1;
   const T kxl = xl ? T(0) : A.kx, kxh = xh ? T(0) : A.kx, kyl = yl ? T(0) : A.ky, kyh = yh ? T(0) : A.ky;
-  // face weights of this column's and row's two faces (0 and n wrap or are walls)
-  T xa[4] = {T(0), T(0.5), T(0.5), T(0)}, xb[4] = {T(0), T(0.5), T(0.5), T(0)};
-  T ya[4] = {T(0), T(0.5), T(0.5), T(0)}, yb[4] = {T(0), T(0.5), T(0.5), T(0)};
-  if (A.c4x) {
+  // fourth order: weights of this column's and row's two faces (0 and n wrap or are walls)
+  T xa[4], xb[4], ya[4], yb[4];
+  if constexpr (ORD4) {
     const int ih = !A.wx && i + 1 == nx ? 0 : i + 1, jh = !A.wy && j + 1 == ny ? 0 : j + 1;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -157,13 +161,21 @@ __global__ void __launch_bounds__(64 * TX * TY) stream_var_kernel(VarArgs<T> A) 
       ya[q] = tab(A.c4y, 4 * j + q);
       yb[q] = tab(A.c4y, 4 * jh + q);
     }
-  }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (xl) xa[q] = T(0);
-    if (xh) xb[q] = T(0);
-    if (yl) ya[q] = T(0);
-    if (yh) yb[q] = T(0);
+    for (int q = 0; q < 4; ++q) {
+      if (xl) xa[q] = T(0);
+      if (xh) xb[q] = T(0);
+      if (yl) ya[q] = T(0);
+      if (yh) yb[q] = T(0);
+    }
+  }
+
+  // (the weights of y are wave-uniform: in tiles of 4 wavefronts they go to vector
+  // registers, which there are enough of, but for look-aheads of 28 levels, where
+  // that would leave a CU two workgroups instead of three)
+  if constexpr (ORD4 && TX == 1 && D != 28) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) asm("" : "+v"(ya[q]), "+v"(yb[q]));
   }
 
   double ring[D + B];
@@ -185,6 +197,10 @@ __global__ void __launch_bounds__(64 * TX * TY) stream_var_kernel(VarArgs<T> A) 
     double em, ea, tkb;
     T cz[4], lz[3], tz;
   };
+  // FP64 in second order with 16-byte copies: the row is read behind the copies,
+  // where fewer scalar registers are in use (moves of spilled ones out of vector
+  // lanes: 2 to 477 a kernel before them, 0 to 27 behind)
+  constexpr bool LATE = sizeof(T) == 8 && !ORD4 && CH == 16;
   auto load_row = [&](int s) {
     const double* rd = (const double*)(A.row + s);
     const T* rt = (const T*)(rd + 4);
@@ -200,30 +216,51 @@ __global__ void __launch_bounds__(64 * TX * TY) stream_var_kernel(VarArgs<T> A) 
     auto at = [&](unsigned o) { return *reinterpret_cast<const T*>(b + o); };
     constexpr unsigned P = L::PF * sz;
     const T fc = at(of + 2 * P + 2 * sz);
-    const T fxm2 = at(of + 2 * P), fxm = at(of + 2 * P + sz), fxp = at(of + 2 * P + 3 * sz), fxp2 = at(of + 2 * P + 4 * sz);
-    const T fym2 = at(of + 2 * sz), fym = at(of + P + 2 * sz), fyp = at(of + 3 * P + 2 * sz), fyp2 = at(of + 4 * P + 2 * sz);
+    T fxm = at(of + 2 * P + sz), fxp = at(of + 2 * P + 3 * sz), fxm2, fxp2, fym2, fyp2;
+    const T fym = at(of + P + 2 * sz), fyp = at(of + 3 * P + 2 * sz);
+    if constexpr (ORD4) {
+      fxm2 = at(of + 2 * P); fxp2 = at(of + 2 * P + 4 * sz);
+      fym2 = at(of + 2 * sz); fyp2 = at(of + 4 * P + 2 * sz);
+    }
     const T pc = at(op + P + sz);
-    const T pxm = at(op + P), pxp = at(op + P + 2 * sz), pym = at(op + sz), pyp = at(op + 2 * P + sz);
+    T pxm = at(op + P), pxp = at(op + P + 2 * sz);
+    const T pym = at(op + sz), pyp = at(op + 2 * P + sz);
     T u0 = at(ou), u1 = at(ou + sz);
     T v0 = at(ov), v1 = at(ov + L::W * sz);
     const T wn = at(ov + (L::gW - L::gV) * L::group);
-    const Row rw = load_row(s);
+    Row rw;
+    if constexpr (!LATE) rw = load_row(s);
     issue(next);
     if (walls) {   // wall faces carry no velocity
       u0 = xl ? T(0) : u0;
       u1 = xh ? T(0) : u1;
       v0 = yl ? T(0) : v0;
       v1 = yh ? T(0) : v1;
+      if constexpr (L::V > 2) {   // (a chunk of four columns: the one beyond the wall is three columns in)
+        fxm = xl ? fc : fxm;
+        fxp = xh ? fc : fxp;
+        pxm = xl ? pc : pxm;
+        pxp = xh ? pc : pxp;
+      }
     }
+    if constexpr (LATE) rw = load_row(s);
     // face s - 1 (cells s - 3 .. s) and level s - 2
-    const T fn = w0 * (rw.cz[0] * t3 + rw.cz[1] * t2 + rw.cz[2] * t1 + rw.cz[3] * fc);
+    T fn;
+    if constexpr (ORD4) fn = w0 * (rw.cz[0] * t3 + rw.cz[1] * t2 + rw.cz[2] * t1 + rw.cz[3] * fc);
+    else fn = w0 * (rw.cz[1] * t2 + rw.cz[2] * t1);
     e = rw.em * ((double)(r2 - rw.tz * (fn - fx)) + rw.tkb) + rw.ea * e;
     asm volatile("" : "+v"(e));   // the level is finished here (keeps the levels' work in order)
     // level s - 1: the explicit z share of the lagged field
     r2 = r1 + (rw.lz[0] * p2 + rw.lz[1] * p1 + rw.lz[2] * pc);
     // level s: x and y
-    const T fxl = xa[0] * fxm2 + xa[1] * fxm + xa[2] * fc + xa[3] * fxp, fxh = xb[0] * fxm + xb[1] * fc + xb[2] * fxp + xb[3] * fxp2;
-    const T fyl = ya[0] * fym2 + ya[1] * fym + ya[2] * fc + ya[3] * fyp, fyh = yb[0] * fym + yb[1] * fc + yb[2] * fyp + yb[3] * fyp2;
+    T fxl, fxh, fyl, fyh;
+    if constexpr (ORD4) {
+      fxl = xa[0] * fxm2 + xa[1] * fxm + xa[2] * fc + xa[3] * fxp, fxh = xb[0] * fxm + xb[1] * fc + xb[2] * fxp + xb[3] * fxp2;
+      fyl = ya[0] * fym2 + ya[1] * fym + ya[2] * fc + ya[3] * fyp, fyh = yb[0] * fym + yb[1] * fc + yb[2] * fyp + yb[3] * fyp2;
+    } else {
+      const T half = T(0.5);
+      fxl = half * (fxm + fc), fxh = half * (fc + fxp), fyl = half * (fym + fc), fyh = half * (fc + fyp);
+    }
     r1 = A.ap * pc + A.ac * fc - ((u1 * fxh - u0 * fxl) * A.tx + (v1 * fyh - v0 * fyl) * A.ty) +
          (kxh * (pxp - pc) - kxl * (pc - pxm)) + (kyh * (pyp - pc) - kyl * (pc - pym));
     asm volatile("" : "+v"(r1), "+v"(r2));
@@ -306,26 +343,26 @@ __global__ void __launch_bounds__(64 * TX * TY) stream_var_kernel(VarArgs<T> A) 
 }
 
 // Launches the kernel of a context's tile shape and look-ahead.
-template <typename T, int TX, int TY, int CH, int Q>
+template <typename T, int TX, int TY, int CH, bool ORD4, int Q>
 hipError_t launch_var_depth(int depth, dim3 grid, const VarArgs<T>& a, hipStream_t s) {
   if constexpr (Q < kStreamDepths) {
     constexpr int D = kStreamDepth[Q];
-    if (depth != Q) return launch_var_depth<T, TX, TY, CH, Q + 1>(depth, grid, a, s);
+    if (depth != Q) return launch_var_depth<T, TX, TY, CH, ORD4, Q + 1>(depth, grid, a, s);
     if constexpr (stream_var_fits(D, TX * TY)) {
-      hipLaunchKernelGGL((stream_var_kernel<T, D, TX, TY, CH>), grid, dim3(64, TX * TY), 0, s, a);
+      hipLaunchKernelGGL((stream_var_kernel<T, D, TX, TY, CH, ORD4>), grid, dim3(64, TX * TY), 0, s, a);
       return hipGetLastError();
     }
   }
   return hipErrorInvalidValue;
 }
 
-template <typename T, int CH>
+template <typename T, int CH, bool ORD4>
 hipError_t launch_var_shape(int shape, int depth, dim3 grid, const VarArgs<T>& a, hipStream_t s) {
   static_assert(kStreamShapes == 4, "one case per shape (the widest holds too many wavefronts)");
   switch (shape) {
-    case 1: return launch_var_depth<T, kStreamShape[1].segs, kStreamShape[1].rows, CH, 0>(depth, grid, a, s);
-    case 2: return launch_var_depth<T, kStreamShape[2].segs, kStreamShape[2].rows, CH, 0>(depth, grid, a, s);
-    case 3: return launch_var_depth<T, kStreamShape[3].segs, kStreamShape[3].rows, CH, 0>(depth, grid, a, s);
+    case 1: return launch_var_depth<T, kStreamShape[1].segs, kStreamShape[1].rows, CH, ORD4, 0>(depth, grid, a, s);
+    case 2: return launch_var_depth<T, kStreamShape[2].segs, kStreamShape[2].rows, CH, ORD4, 0>(depth, grid, a, s);
+    case 3: return launch_var_depth<T, kStreamShape[3].segs, kStreamShape[3].rows, CH, ORD4, 0>(depth, grid, a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -333,8 +370,10 @@ hipError_t launch_var_shape(int shape, int depth, dim3 grid, const VarArgs<T>& a
 template <typename T>
 hipError_t launch_stream_var(int shape, int depth, dim3 grid, const VarArgs<T>& a, hipStream_t s) {
   const uintptr_t p = (uintptr_t)a.f | (uintptr_t)a.p | (uintptr_t)a.u | (uintptr_t)a.v | (uintptr_t)a.w;
-  if (((uintptr_t)a.nx * sizeof(T)) % 16 == 0 && p % 16 == 0) return launch_var_shape<T, 16>(shape, depth, grid, a, s);
-  return launch_var_shape<T, 4>(shape, depth, grid, a, s);
+  const bool wide = ((uintptr_t)a.nx * sizeof(T)) % 16 == 0 && p % 16 == 0;
+  if (a.c4x)
+    return wide ? launch_var_shape<T, 16, true>(shape, depth, grid, a, s) : launch_var_shape<T, 4, true>(shape, depth, grid, a, s);
+  return wide ? launch_var_shape<T, 16, false>(shape, depth, grid, a, s) : launch_var_shape<T, 4, false>(shape, depth, grid, a, s);
 }
 
 }  // namespace stream
