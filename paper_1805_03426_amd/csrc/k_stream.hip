@@ -3,6 +3,8 @@
 // k_stream64.hip and k_stream32.hip).
 #include "stream_variant.h"
 
+#include <math.h>
+
 #include <algorithm>
 
 namespace mr {
@@ -27,6 +29,12 @@ extern template hipError_t launch_stream_var<float>(int, int, dim3, const VarArg
 // idle or a second round for half of them).  400^3 FP64: 256 x 4 and 1 segment
 // 587 us, 128 x 4 692; 576^3 FP64: 192 x 4 1.83 ms, 256 x 4 2.06; 450 x 300 x
 // 200 FP32: 192 x 4 154 us, 128 x 4 183 (300 workgroups on 256 CUs).
+// The estimate that goes with the plan (us) takes a level's time on a CU that holds
+// one workgroup (alone_us), or several, from steps timed at 66 grids and four
+// look-aheads each (medians by shape); the choice among plans leaves the 64-column
+// tiles more than they take alone (one_us), which the estimate must not.  Copies of 4
+// bytes take 1.6 times as long (FP64) and 1.1 (FP32).  Look-aheads of 60 levels leave
+// a CU two workgroups of 4 wavefronts at a time.
 // Variants (walls, fourth order, explicit z): 186^3 FP64 192 x 4 columns and 4
 // segments 66 us, 3 segments 76, 64 x 4 and 3 segments 68; 128 x 4 and 5, 82.
 StreamPlan stream_plan(int nx, int ny, int nz, bool f64, bool variant, int cus, int depth, const std::vector<int> (&before)[2],
@@ -35,12 +43,15 @@ StreamPlan stream_plan(int nx, int ny, int nz, bool f64, bool variant, int cus, 
     double one_us;    // a level of the only workgroup of a CU
     double more_us;   // a level for each workgroup of a CU that holds several
     double rate;      // bytes per us of a full GPU
+    double alone_us, shared_us;   // one_us and more_us of the estimate
   };
-  static const Shape s64[kStreamShapes] = {{1.40, 1.40, 5.6e6}, {1.13, 1.13, 5.5e6}, {0.72, 0.72, 5.35e6}, {0.60, 0.33, 5.0e6}};
-  static const Shape s32[kStreamShapes] = {{0.70, 0.70, 5.6e6}, {0.70, 0.60, 5.5e6}, {0.61, 0.38, 5.35e6}, {0.55, 0.25, 5.0e6}};
+  static const Shape s64[kStreamShapes] = {{1.40, 1.40, 5.6e6, 1.37, 1.37}, {1.13, 1.13, 5.5e6, 1.13, 1.13},
+                                           {0.72, 0.72, 5.35e6, 0.66, 0.66}, {0.60, 0.33, 5.0e6, 0.43, 0.28}};
+  static const Shape s32[kStreamShapes] = {{0.70, 0.70, 5.6e6, 0.80, 0.75}, {0.70, 0.60, 5.5e6, 0.67, 0.60},
+                                           {0.61, 0.38, 5.35e6, 0.58, 0.44}, {0.55, 0.25, 5.0e6, 0.40, 0.22}};
   // the variants' kernels (three shapes; FP64 with 4-byte copies takes 1.6 times as long a level)
-  static const Shape v64[kStreamShapes] = {{}, {0.95, 0.95, 5.5e6}, {0.68, 0.68, 5.5e6}, {0.60, 0.42, 5.0e6}};
-  static const Shape v32[kStreamShapes] = {{}, {0.70, 0.62, 5.5e6}, {0.55, 0.45, 5.35e6}, {0.48, 0.22, 5.0e6}};
+  static const Shape v64[kStreamShapes] = {{}, {0.95, 0.95, 5.5e6, 0.86, 0.86}, {0.68, 0.68, 5.5e6, 0.67, 0.67}, {0.60, 0.42, 5.0e6, 0.57, 0.42}};
+  static const Shape v32[kStreamShapes] = {{}, {0.70, 0.62, 5.5e6, 0.70, 0.62}, {0.55, 0.45, 5.35e6, 0.55, 0.44}, {0.48, 0.22, 5.0e6, 0.41, 0.22}};
   const double slow = variant && f64 && nx % 2 ? 1.6 : 1.0;
   const Shape* sh = variant ? (f64 ? v64 : v32) : (f64 ? s64 : s32);
   const double sz = f64 ? 8.0 : 4.0;
@@ -74,6 +85,10 @@ StreamPlan stream_plan(int nx, int ny, int nz, bool f64, bool variant, int cus, 
       const double us = std::max(mem, (levels + 6) * slow * std::max(sh[q].one_us, per_cu * sh[q].more_us));
       if (best_us < 0.0 || us < best_us) {
         best_us = us;
+        const double narrow = f64 ? (nx % 2 ? 1.6 : 1.0) : (nx % 4 ? 1.1 : 1.0);
+        const bool pairs = kStreamDepth[depth] > 44 && waves == 4 && per_cu > 1.0;   // two at a time on a CU
+        const double busy = sh[q].shared_us * (pairs ? 2.0 * ceil(per_cu / 2.0) : per_cu);
+        p.us = std::max(mem, (levels + 6) * narrow * std::max(sh[q].alone_us, busy));
         best = p;
       }
     }

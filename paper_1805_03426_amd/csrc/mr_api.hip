@@ -509,6 +509,34 @@ int choose_chunks(int nz, int64_t tiles, int cus, bool plain64, int& L, int& nch
   return MR_OK;
 }
 
+// One step of the line solver in us, estimated: the longest of
+//   - one chunk's walk (a level 1.1 us in FP64, 0.58 in FP32), longer where more
+//     than 8 wavefronts share a CU's registers;
+//   - the levels that the fullest CU walks, at what a wavefront's level takes of a
+//     busy CU (0.175 us, 0.092), five more a tile for its start and end;
+//   - the six values of every cell from memory (3.8 and 4.3 TB/s);
+// a tenth more where rows are not whole 64-byte lines, and for the variants.  In us,
+// estimated and timed: FP64 64 x 64 x 256 38 and 37, 128^3 22 and 25, 186^3 108 and
+// 102, 200^3 120 and 114, 320 x 320 x 64 85 and 77, 96 x 96 x 300 58 and 58, 256^3
+// 212 and 199; FP32 128^3 12 and 14, 150^3 33 and 35, 200^3 84 and 77, 64 x 64 x 512
+// 37 and 35, 256^3 96 and 96.
+double line_us(const Problem& P, const mr_desc* d, int64_t tiles, int cus, int L, int nch) {
+  const bool f64 = d->precision == MR_FP64, ord4 = d->face_order == 4, expz = d->z_explicit > 0.0;
+  const double k = 1.0 + (ord4 && f64 ? 0.1 : 0.0) + (expz ? 0.15 : 0.0);
+  const double cells = (double)P.x.n * P.y.n * P.z.n, levels = k * nch * L;
+  const double fill = std::min(1.0, (double)tiles / cus), rounds = (double)((tiles + cus - 1) / cus);
+  double chunk = f64 ? 3.0 + 1.1 * L * k : std::max(11.0, 3.0 + 0.58 * L * k);
+  if (nch > 8) {
+    chunk *= 1.0 + (f64 ? 0.1 * (nch - 8) : P.sweep_ok ? 0.07 * (nch - 8) : 0.18 * std::min(nch - 8, 2));
+    chunk *= 1.0 + 0.45 * std::min(fill, 0.6);
+    if ((ord4 || expz) && nch > 12) chunk *= 1.4;   // (128 registers a lane: these kernels spill)
+  }
+  const double walked = tiles > cus ? (f64 ? 0.175 : 0.092) * rounds * (levels + 5.0 * k)
+                                    : levels * (f64 ? 0.115 + 0.06 * fill : 0.055 + 0.037 * fill);
+  const double mem = cells * (f64 ? 48.0 / 3.8e6 : 24.0 / 4.3e6);
+  return std::max({chunk, walked, mem}) * (P.x.n * (f64 ? 8 : 4) % 64 ? 1.1 : 1.0);
+}
+
 // Byte buffer that hands out 256-byte aligned slots.
 struct Packer {
   vector<char> buf;
@@ -800,6 +828,33 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   double taus[mr::NKINDS];
   const int nz = P.z.n;
   const bool f64 = desc->precision == MR_FP64;
+  // the implicit z systems of the step kinds and their factors
+  struct Kind {
+    vector<double> sub, diag, sup, bz, tsub, tsup;
+    SweepHost sh, sht;
+  };
+  vector<Kind> kinds(mr::NKINDS);
+  for (int kind = 0; kind < mr::NKINDS; ++kind) {
+    Kind& q = kinds[kind];
+    const double tau = kind_tau(kind, desc->dt);
+    taus[kind] = tau;
+    const double tk = tau * P.kappa;
+    for (vector<double>* v : {&q.sub, &q.diag, &q.sup, &q.bz, &q.tsub, &q.tsup}) v->assign(nz, 0.0);
+    // the implicit share (1 - w) of the z diffusion; the wall source stays whole
+    z_system(P.z, desc, tk * (1.0 - desc->z_explicit), q.sub.data(), q.diag.data(), q.sup.data(), q.bz.data());
+    if (!sweep_factors(nz, q.sub.data(), q.diag.data(), q.sup.data(), q.sh)) return MR_EINVAL;
+    q.sh.tkb.assign(nz, 0.0);
+    for (int k = 0; k < nz; ++k) q.sh.tkb[k] = tk * q.bz[k];
+    // transpose: sub^T_k = sup_{k-1}, sup^T_k = sub_{k+1}
+    for (int k = 0; k < nz; ++k) {
+      q.tsub[k] = k > 0 ? q.sup[k - 1] : 0.0;
+      q.tsup[k] = k < nz - 1 ? q.sub[k + 1] : 0.0;
+    }
+    // (the reverse steps' systems: no wall source)
+    if (!sweep_factors(nz, q.tsub.data(), q.diag.data(), q.tsup.data(), q.sht)) return MR_EINVAL;
+    q.sht.tkb.assign(nz, 0.0);
+  }
+
   // the streaming step runs wherever it applies but on small grids where the
   // line solver is faster: FP64 with copies into LDS of 4 bytes (odd N_x): 127^3
   // 54 us against 30, 175^3 86 against 99; FP64 columns of at most 64 levels in
@@ -812,10 +867,9 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   // 36.4, 200 x 200 x 100 28.2 against 48.5)
   const bool one_round = ltiles <= cus;
   const int64_t cells = (int64_t)P.x.n * P.y.n * nz;
-  const bool streams = P.sweep_ok && desc->step_method == 0 &&
-                       (nch == 0 || cells >= 4500000 ||
-                        (f64 ? P.x.n % 2 == 0 && !(one_round && nz <= 64)
-                             : (one_round ? nz > 128 : cells >= 2500000)));
+  bool streams = P.sweep_ok && desc->step_method == 0 &&
+                 (nch == 0 || cells >= 4500000 ||
+                  (f64 ? P.x.n % 2 == 0 && !(one_round && nz <= 64) : (one_round ? nz > 128 : cells >= 2500000)));
   // the variants' forward step streams (x and y of uniform widths) on grids of
   // 2.5e6 cells and more (FP64 with 4-byte copies 4.5e6) and on tall columns in
   // one round of tiles.  One step in us, line solver against streaming, with walls,
@@ -827,8 +881,8 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   // and 18; FP64 odd: 187^3 134 and 82 / 106 and 81, 301 x 280 x 30 44 and 45 / 39
   // and 45
   const bool copies4 = f64 && P.x.n % 2 != 0;
-  const bool streamv = !P.sweep_ok && desc->step_method == 0 && nch > 0 && uniform_axis(P.x) && uniform_axis(P.y) &&
-                       (cells >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));
+  bool streamv = !P.sweep_ok && desc->step_method == 0 && nch > 0 && uniform_axis(P.x) && uniform_axis(P.y) &&
+                 (cells >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));
   size_t vro[mr::NKINDS], vcbo[mr::NKINDS];
   const vector<double> ihz = inv(P.z.h);
   size_t sro[2][2][mr::NKINDS], scbo[2][2][mr::NKINDS];   // streaming tables: [transposed][down][kind]
@@ -836,12 +890,36 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   int ahead = 0;                                      // the streaming step's look-ahead
   vector<int> after[2], before[2];                    // its reach after / before each walk position
   for (int d = 0; d < 2; ++d) after[d].assign(nz, 0), before[d].assign(nz, 0);
-  // (`ahead` covers the walk directions and step kinds added so far)
-  auto add_reach = [&](const StreamHost& w, int d) {
+  auto add_reach = [&](const SweepHost& h, int d) {
+    const StreamHost w = stream_walk(h, d);
     reach(nz, [&](int k) { return w.cb[k]; }, eps, [&](int k) -> int& { return after[d][k]; });
     reach(nz, [&](int k) { return w.a[nz - 1 - k]; }, eps, [&](int k) -> int& { return before[d][nz - 1 - k]; });
     ahead = std::max(ahead, *std::max_element(after[d].begin(), after[d].end()));
   };
+  // the streaming step's look-ahead, tiles and z segments
+  int stream_d = 0;
+  mr::StreamPlan plan;
+  if (streams || streamv) {
+    for (const Kind& q : kinds) {
+      add_reach(q.sh, 0);
+      for (int d = 0; d < 2 && streams; ++d) add_reach(q.sht, d);
+      if (streams) add_reach(q.sh, 1);
+    }
+    for (int d = mr::kStreamDepths; d > 0; --d)
+      if (ahead <= mr::kStreamDepth[d - 1]) stream_d = d;
+    if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, streamv, cus, stream_d - 1, before, after);
+    // the bounds above hold for look-aheads of up to 16 levels; a longer one is walked
+    // by every segment of a column, and takes a CU's registers: then the estimates
+    // decide.  One step in us, line solver and streaming, by the look-ahead: FP64
+    // 128^3 25 and 36 (16 levels), 46 (28), 44 (44), 57 (60), 192^3 96 and 87, 93, 97,
+    // 110, 64 x 64 x 256 37 and 23, 30, 38, 48; FP32 186^3 55 and 48, 65, 67, 78, 160 x
+    // 160 x 200 38 and 34, 44, 52, 61; with walls, FP64 96 x 96 x 160 30 and 52 (28)
+    if (stream_d == 0 || (nch > 0 && plan.us > line_us(P, desc, ltiles, cus, L, nch))) {
+      streams = streamv = false;
+      stream_d = 0;
+      plan = mr::StreamPlan();
+    }
+  }
   // (one allocation for the streaming tables: 13 sets of rows and back factors)
   if (streams) pk.buf.reserve(pk.buf.size() + 16 * (size_t)(nz + 2 * mr::kStreamPad) * (sizeof(mr::StreamRow<double>) + 64));
   auto pack_stream = [&](const SweepHost& h, int kind, bool rev) {
@@ -850,44 +928,25 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
       const StreamHost w = stream_walk(h, d);
       sro[rev][d][kind] = f64 ? pk.put(stream_rows<double>(ihz, h, w, rev, d)) : pk.put(stream_rows<float>(ihz, h, w, rev, d));
       scbo[rev][d][kind] = pk.put(stream_cb(w));
-      add_reach(w, d);
     }
   };
-  vector<double> sub(nz), diag(nz), sup(nz), bz(nz), tsub(nz), tsup(nz);
   for (int kind = 0; kind < mr::NKINDS; ++kind) {
-    const double tau = kind_tau(kind, desc->dt);
-    taus[kind] = tau;
-    const double tk = tau * P.kappa;
-    // the implicit share (1 - w) of the z diffusion; the wall source stays whole
-    z_system(P.z, desc, tk * (1.0 - desc->z_explicit), sub.data(), diag.data(), sup.data(), bz.data());
-    SweepHost sh;
-    if (!sweep_factors(nz, sub.data(), diag.data(), sup.data(), sh)) return MR_EINVAL;
-    sh.tkb.assign(nz, 0.0);
-    for (int k = 0; k < nz; ++k) sh.tkb[k] = tk * bz[k];
-    swo[kind] = pack_sweep(pk, sh);
-    pack_stream(sh, kind, false);
+    const Kind& q = kinds[kind];
+    swo[kind] = pack_sweep(pk, q.sh);
+    pack_stream(q.sh, kind, false);
     if (streamv) {
-      const StreamHost w = stream_walk(sh, false);
-      vro[kind] = f64 ? pk.put(variant_rows<double>(P, desc, sh, tau)) : pk.put(variant_rows<float>(P, desc, sh, tau));
-      vcbo[kind] = pk.put(stream_cb(w));
-      add_reach(w, 0);
+      const double tau = taus[kind];
+      vro[kind] = f64 ? pk.put(variant_rows<double>(P, desc, q.sh, tau)) : pk.put(variant_rows<float>(P, desc, q.sh, tau));
+      vcbo[kind] = pk.put(stream_cb(stream_walk(q.sh, false)));
     }
-    // transpose: sub^T_k = sup_{k-1}, sup^T_k = sub_{k+1}
-    for (int k = 0; k < nz; ++k) {
-      tsub[k] = k > 0 ? sup[k - 1] : 0.0;
-      tsup[k] = k < nz - 1 ? sub[k + 1] : 0.0;
-    }
-    SweepHost sht;   // the reverse steps' systems: no wall source
-    if (!sweep_factors(nz, tsub.data(), diag.data(), tsup.data(), sht)) return MR_EINVAL;
-    sht.tkb.assign(nz, 0.0);
-    swto[kind] = pack_sweep(pk, sht);
-    pack_stream(sht, kind, true);
+    swto[kind] = pack_sweep(pk, q.sht);
+    pack_stream(q.sht, kind, true);
     if (nch == 0) continue;
     ZHost zh, th;
-    if (!z_factors(nz, L, sub.data(), diag.data(), sup.data(), zh)) return MR_EINVAL;
+    if (!z_factors(nz, L, q.sub.data(), q.diag.data(), q.sup.data(), zh)) return MR_EINVAL;
     zh.tkb.assign((size_t)nch * L, 0.0);
-    for (int k = 0; k < nz; ++k) zh.tkb[k] = tk * bz[k];
-    if (!z_factors(nz, L, tsub.data(), diag.data(), tsup.data(), th)) return MR_EINVAL;
+    std::copy(q.sh.tkb.begin(), q.sh.tkb.end(), zh.tkb.begin());
+    if (!z_factors(nz, L, q.tsub.data(), q.diag.data(), q.tsup.data(), th)) return MR_EINVAL;
     th.tkb.assign((size_t)nch * L, 0.0);
     zfo[kind] = pack_z(pk, zh);
     zto[kind] = pack_z(pk, th);
@@ -904,14 +963,6 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     const StreamHost w = stream_walk(shid, false);
     o_sid = f64 ? pk.put(stream_rows<double>(ihz, shid, w, true, false)) : pk.put(stream_rows<float>(ihz, shid, w, true, false));
     o_sidcb = pk.put(stream_cb(w));
-  }
-  // the streaming step's look-ahead, tiles and z segments
-  int stream_d = 0;
-  mr::StreamPlan plan;
-  if (streams || streamv) {
-    for (int d = mr::kStreamDepths; d > 0; --d)
-      if (ahead <= mr::kStreamDepth[d - 1]) stream_d = d;
-    if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, streamv, cus, stream_d - 1, before, after);
   }
   const size_t o_seg[2] = {pk.put(plan.seg[0]), pk.put(plan.seg[1])};
   vector<double> dcz(P.z.dc);

@@ -159,6 +159,7 @@ struct alignas(64) VarRow {
 // first position, end, walk start, walk end.
 struct StreamPlan {
   int shape = 0, nseg = 1;
+  double us = 0.0;   // one step, estimated
   std::vector<int> seg[2];
 };
 // before[d][s] / after[d][s]: how far before / after position s of walk

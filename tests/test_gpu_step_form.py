@@ -41,3 +41,13 @@ def test_unknown_call_is_refused():
     with _ctx((32, 8, 16)) as ctx:
         for call in (-1, 4):
             assert _lib.lib().mr_get_step_form(ctx._ctx, call, byref(out)) == _lib.MR_EINVAL
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_long_look_ahead_takes_the_line_solver(prec):
+    """One round of 256 levels: segments of short look-aheads stream faster, of long
+    ones (58 levels at r = 2) slower than the line solver."""
+    print("case step forms look-ahead", prec, flush=True)
+    assert _forms((64, 64, 256), r=0.05, precision=prec) == ("stream",) * 4
+    assert _forms((64, 64, 256), r=2.0, precision=prec) == ("line",) * 4
+    assert _forms((64, 64, 700), r=2.0, precision=prec) == ("stream",) * 4   # beyond the line solver
