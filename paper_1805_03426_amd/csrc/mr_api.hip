@@ -496,11 +496,19 @@ vector<double> stream_cb(const StreamHost& w) {
 // 106; side walls, fourth-order faces and an explicit z share at 186^3 134 to
 // 160, 78 to 101; the same at 251 x 251 x 128 with chunks of 16 (8 of them)
 // instead of 32 (4): 133 to 122.
-int choose_chunks(int nz, int64_t tiles, int cus, bool plain64, int& L, int& nch) {
-  const int most = tiles <= cus ? 8 : 4;
+// FP64 with 3 to 4 tiles a CU: two chunks for 33 to 64 levels (the tiles are all
+// resident and the CU has its 8 wavefronts): 256 x 256 x 64 48.8 us with chunks of
+// 16, 42.9 with 32; 224 x 224 x 64 44.9 and 39.5; 256 x 256 x 48 36.6 and 33.6 with
+// 24; at 3 tiles and fewer a CU 16 is the faster or level (192 x 256 x 64 in fourth
+// order 36 and 41).  There, 65 to 96 levels in second order: 32, not 24, whose reverse
+// step takes 82 us against 69 with walls at 256 x 256 x 96 (forward 70 and 68).
+int choose_chunks(int nz, int64_t tiles, int cus, bool f64, bool plain, bool ord4, int& L, int& nch) {
+  const bool plain64 = f64 && plain, resident = f64 && tiles > 3 * (int64_t)cus && tiles <= 4 * (int64_t)cus;
+  const int most = tiles <= cus ? 8 : resident && nz > 32 && nz <= 64 ? 2 : 4;
+  const bool no24 = most == 4 && (plain64 || (resident && !ord4));
   L = 0;
   for (int l : mr::kChunkLens)
-    if (!L && l <= 32 && l * most >= nz && (l != 24 || most == 8 || !plain64)) L = l;
+    if (!L && l <= 32 && l * most >= nz && (l != 24 || !no24)) L = l;
   if (!L && 24 * 8 >= nz && (!plain64 || nz > 160)) L = 24;
   for (int l : mr::kChunkLens)
     if (!L && l >= 32 && l * mr::kMaxChunks >= nz) L = l;
@@ -811,7 +819,8 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     cus = 256;
   const int lrows = desc->precision == MR_FP64 ? 2 : 1, lcols = mr::kWave / lrows;   // patch of a line workgroup
   const int64_t ltiles = (int64_t)((P.x.n + lcols - 1) / lcols) * ((P.y.n + lrows - 1) / lrows);
-  if (choose_chunks(P.z.n, ltiles, cus, desc->precision == MR_FP64 && P.sweep_ok, L, nch) != MR_OK) L = nch = 0;
+  if (choose_chunks(P.z.n, ltiles, cus, desc->precision == MR_FP64, P.sweep_ok, desc->face_order == 4, L, nch) != MR_OK)
+    L = nch = 0;
   const int npad = std::max(nch * L, P.z.n);
 
   vector<double> R[3];
