@@ -580,8 +580,11 @@ void launch_eo(bool expz, bool ord4, dim3 grid, dim3 block, hipStream_t s, const
 // of at most 8 chunks launch them compiled for 512 threads (up to 256 VGPRs,
 // no spill), columns of 9 to 12 for 768 (up to 168: at 150 x 150 x 300 in FP64
 // the reverse step with walls, fourth order and explicit z takes 190 us instead
-// of 453, the forward one 152 instead of 180).  The plain uniform-width kernels
-// fit either way and stay at 1024.
+// of 453, the forward one 152 instead of 180).  In FP32 only those with fourth-order
+// faces (96 x 96 x 300 forward 32.0 us and 36.0, reverse 39.6 and 43.0): the others
+// fit into 128 and are slower compiled for 768 (stretched x and y at 32 x 32 x 300
+// forward 29.9 and 24.0, explicit z share 35.6 and 34.2, walls reverse 32.9 and 31.9).
+// The plain uniform-width kernels fit either way and stay at 1024.
 template <typename T, int LL, int MODE, int R, int MB, int PF, int MT>
 void launch_variant(bool walls, bool expz, bool ord4, bool uxy, dim3 grid, dim3 block, hipStream_t s,
                     const LineArgs<T>& a) {
@@ -661,7 +664,7 @@ hipError_t launch_line(mr_ctx* c, LineArgs<T> a, hipStream_t s) {
     if (c->nch <= 8) return launch_variant<T, LL, MODE, rows, mb, pf, 512>(walls, expz, ord4, uxy, grid, block, s, a);
     if constexpr (LL >= 32) {   // shorter chunks come at most 8 to a column
       if constexpr (LL == 32)
-        if (c->nch <= 12) return launch_variant<T, LL, MODE, rows, mb, pf, 768>(walls, expz, ord4, uxy, grid, block, s, a);
+        if (c->nch <= 12 && (sizeof(T) == 8 || ord4)) return launch_variant<T, LL, MODE, rows, mb, pf, 768>(walls, expz, ord4, uxy, grid, block, s, a);
       launch_variant<T, LL, MODE, rows, mb, pf, 1024>(walls, expz, ord4, uxy, grid, block, s, a);
     }
   };
