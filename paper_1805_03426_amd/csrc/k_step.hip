@@ -375,13 +375,15 @@ void launch_grad_form(mr_ctx* c, const GradArgs<T>& a, int most, hipStream_t s) 
 // registers would not fit beside the accumulators at 4 wavefronts per SIMD):
 // 256^3, 3, 5 and 10 steps 357, 495 and 835 us against 380, 540 and 935 without
 // the loads ahead.
-// FP32: on small grids (less than 4 workgroups a CU of the large form) the same,
-// one segment per workgroup: 10 steps at 80 x 81 x 50 30 us against 60, 128^3 54
-// against 66.  5 to 8 steps: segments of 4 levels, loads ahead, runs of 4 with the
-// level below carried: 256^3, 5 steps 262 us against 278, 1024 x 1024 x 512 8.47 ms
-// against 8.57.  Fewer or more steps: segments of 8 levels, runs of 2, loads of
-// the step itself (3 steps at 1024 x 1024 x 512 6.7 ms against 7.1, 10 steps 14.0
-// against 15.7, where the carry beside the loads ahead spills).
+// FP32: where the large form (8 levels, runs of 2; two workgroups a CU at a time)
+// makes one or two rounds and fills the last one to 4/5 at most, the same, one segment
+// per workgroup: 10 steps at 80 x 81 x 50 30 us against 60, 128^3 (a round half full)
+// 40 against 49, 150^3 (two, 0.56) 79 against 95; but 90 x 90 x 300 (0.89) 68 against 60,
+// 256 x 256 x 64 (one full round) 72 against 62.  Else 5 to 8 steps: segments of 4 levels,
+// loads ahead, runs of 4 with the level below carried: 256^3, 5 steps 262 us against
+// 278, 1024 x 1024 x 512 8.47 ms against 8.57.  Fewer or more steps: segments of 8 levels,
+// runs of 2, loads of the step itself (3 steps at 1024 x 1024 x 512 6.7 ms against 7.1,
+// 10 steps 14.0 against 15.7, where the carry beside the loads ahead spills).
 template <typename T, int KM>
 void launch_grad_seg(mr_ctx* c, const GradArgs<T>& a, hipStream_t s) {
   if constexpr (sizeof(T) == 8) {
@@ -389,7 +391,8 @@ void launch_grad_seg(mr_ctx* c, const GradArgs<T>& a, hipStream_t s) {
   } else {
     const int64_t wgs = (int64_t)((c->nx + kWave - 1) / kWave) * ((c->ny + kGradRows - 1) / kGradRows) *
                         ((c->nz + 8 * kGradRun - 1) / (8 * kGradRun));
-    if (wgs < 4 * 256) launch_grad_form<T, KM, 4, false, true>(c, a, 1, s);
+    const int64_t round = 2 * 256, rounds = (wgs + round - 1) / round;
+    if (rounds <= 2 && 5 * wgs <= 4 * rounds * round) launch_grad_form<T, KM, 4, false, true>(c, a, 1, s);
     else if constexpr (KM == 8) launch_grad_form<T, KM, 4, true, true>(c, a, 4, s);
     else launch_grad_form<T, KM, 8, true, false>(c, a, kGradRun, s);
   }
