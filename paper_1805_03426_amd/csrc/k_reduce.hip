@@ -261,39 +261,42 @@ __global__ void __launch_bounds__(256) nu_partial(const T* th, const T* w, const
   }
 }
 
-// One workgroup: Nu_k of every face from the partials, kNuLanes lanes a face
-// (each merges every kNuLanes-th partial, then a shuffle tree), then the summary
-// sums as a fixed tree (per-thread strided double-double sums, wave shuffles,
-// then the wavefronts in order).  Per-face values stay in LDS.  With one thread
-// a face (256 in all) it took 16-17 us for 200 to 256 levels, waiting on 33 to
-// 64 partials one after the other.
+// One workgroup: Nu_k of every face from the partials, LANES lanes a face (each
+// merges every LANES-th partial, then a shuffle tree), then the summary sums as a
+// fixed tree (per-thread strided double-double sums, wave shuffles, then the
+// wavefronts in order).  Per-face values stay in LDS.  Up to 1024 threads, four
+// lanes a face: with one thread a face (256 in all) it took 16-17 us for 200 to 256
+// levels, waiting on 33 to 64 partials one after the other.  With less than four
+// partials a face, one lane and up to 256 threads: the Nusselt profile of 32 x 32 x
+// 300 15.3 us with 1024, 11.0 with 256.
 constexpr int kNuMaxFaces = 1024;
 constexpr int kNuFinal = 1024;
 constexpr int kNuLanes = 4;
 
-__global__ void __launch_bounds__(kNuFinal) nu_final(const double* part, int P, int nz,
+template <int LANES>
+__global__ void __launch_bounds__(LANES * (kNuFinal / kNuLanes)) nu_final(const double* part, int P, int nz,
                                                      const double* dcz, const double* hz, double atot,
                                                      double atot_lo, double sq, int dir_bot, int dir_top, double t_bot,
                                                      double t_top, double* prof) {
   __shared__ double s_nu[kNuMaxFaces + 1];   // the convective flux sums, then Nu_k
   __shared__ DD s_mean[kNuMaxFaces];
-  __shared__ DD scratch[4][kNuFinal / kWave];
+  __shared__ DD scratch[4][LANES * (kNuFinal / kNuLanes) / kWave];
   __shared__ double total[4];
-  const int sub = threadIdx.x % kNuLanes;
-  for (int k0 = 0; k0 < nz; k0 += (int)blockDim.x / kNuLanes) {
-    const int k = k0 + (int)threadIdx.x / kNuLanes;
+  const int sub = threadIdx.x % LANES;
+  for (int k0 = 0; k0 < nz; k0 += (int)blockDim.x / LANES) {
+    const int k = k0 + (int)threadIdx.x / LANES;
     const int kc = min(k, nz - 1);
     DD conv{0.0, 0.0}, mean{0.0, 0.0};
 #pragma unroll 4
-    for (int p = sub; p < P; p += kNuLanes) {
+    for (int p = sub; p < P; p += LANES) {
       const double* o = part + ((size_t)kc * P + p) * 4;
       conv = dd_merge(conv, DD{o[0], o[1]});
       mean = dd_merge(mean, DD{o[2], o[3]});
     }
 #pragma unroll
-    for (int off = kNuLanes / 2; off > 0; off >>= 1) {
-      conv = dd_merge(conv, DD{__shfl_down(conv.s, off, kNuLanes), __shfl_down(conv.c, off, kNuLanes)});
-      mean = dd_merge(mean, DD{__shfl_down(mean.s, off, kNuLanes), __shfl_down(mean.c, off, kNuLanes)});
+    for (int off = LANES / 2; off > 0; off >>= 1) {
+      conv = dd_merge(conv, DD{__shfl_down(conv.s, off, LANES), __shfl_down(conv.c, off, LANES)});
+      mean = dd_merge(mean, DD{__shfl_down(mean.s, off, LANES), __shfl_down(mean.c, off, LANES)});
     }
     if (sub == 0 && k < nz) {
       s_nu[k] = conv.s + conv.c;
@@ -388,8 +391,10 @@ void nusselt_kernels(mr_ctx* c, const void* th, const void* w, double* prof, dou
     hipLaunchKernelGGL(k, grid, block, 0, s, (const float*)th, (const float*)w, c->hx64, c->areaw, c->nx, c->ny,
                        c->nz, P, part);
   }
-  const int nf = std::min(kNuFinal, (c->nz * kNuLanes + kWave - 1) / kWave * kWave);
-  hipLaunchKernelGGL(nu_final, dim3(1), dim3(nf), 0, s, (const double*)part, P, c->nz, c->dcz, c->hz64, c->atot,
+  const int lanes = P < kNuLanes ? 1 : kNuLanes;
+  const int nf = std::min(kNuFinal / kNuLanes * lanes, (c->nz * lanes + kWave - 1) / kWave * kWave);
+  auto fin = lanes == 1 ? nu_final<1> : nu_final<kNuLanes>;
+  hipLaunchKernelGGL(fin, dim3(1), dim3(nf), 0, s, (const double*)part, P, c->nz, c->dcz, c->hz64, c->atot,
                      c->atot_lo, sqrt(c->ra * c->pr), c->bc_bot == MR_DIRICHLET, c->bc_top == MR_DIRICHLET, c->t_bot, c->t_top,
                      prof);
 }
