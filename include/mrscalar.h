@@ -203,7 +203,9 @@ int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_c
  * outs[0] and th_cur, outs[q] from outs[q-1] and outs[q-2]): a ring of three
  * buffers satisfies this.  Results equal count calls of mr_scalar_step to
  * rounding.  Where mr_scalar_step is one streaming kernel, so is each step here
- * (nothing is allocated).  Otherwise:
+ * (nothing is allocated), but for flat grids (FP64 up to 3 levels, FP32 up to 4)
+ * whose sweep tiles keep the GPU full: sweeps, as below, outside a stream capture or
+ * once their fields are allocated.  Otherwise:
  * with step_method 2, and with step_method 0 on grids whose sweep tiles keep
  * the GPU full (at least 16 wavefronts per CU, rounds of tiles at least 3/4
  * full: 576 x 576 and 1024 x 1024 columns, not 256 x 256) or columns too tall
@@ -252,7 +254,7 @@ int mr_scalar_step_backward(mr_ctx* ctx, int64_t n, const void* mu_next, const v
  * mu_cur and mu_next, outs[1] from outs[0] and mu_cur, outs[q] from outs[q-1]
  * and outs[q-2]).  Results equal count calls of mr_scalar_step_backward to
  * rounding.  Where the plain mr_scalar_step is one streaming kernel, so is each
- * reverse step here.  Otherwise, where the context runs step sequences as column sweeps
+ * reverse step here (but for the flat grids of mr_scalar_steps).  Otherwise, where the context runs step sequences as column sweeps
  * (mr_get_step_method 2) the reverse steps run as column sweeps too: each
  * kernel back-substitutes the previous reverse step's transposed solve while
  * it eliminates its own the other way (7 values per cell and step), with the

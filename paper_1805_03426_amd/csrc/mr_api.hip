@@ -742,7 +742,8 @@ int mr_get_step_method(const mr_ctx* ctx, int32_t* method) {
 int mr_get_step_form(const mr_ctx* ctx, int32_t call, int32_t* form) {
   if (!ctx || !form || call < 0 || call > 3) return MR_EINVAL;
   const bool back = call >= 2, sequence = call & 1;
-  if (ctx->stream_d || (!back && ctx->stream_v)) *form = 3;
+  if (sequence && ctx->sweep_flat) *form = 2;
+  else if (ctx->stream_d || (!back && ctx->stream_v)) *form = 3;
   else if (sequence ? ctx->sweep_pref : back ? ctx->nch == 0 : ctx->sweep_single) *form = 2;
   else *form = 1;
   return MR_OK;
@@ -1049,6 +1050,11 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
   c->sweep_single = nch == 0 || desc->step_method == 2;
   c->stream_d = streams ? stream_d : 0;
   c->stream_v = streamv ? stream_d : 0;
+  // a streaming step walks 8 levels at least and one behind: sequences on flat grids
+  // whose sweep tiles keep the GPU full run as sweeps, us a step FP64 / FP32: 1024 x
+  // 1024 columns of 2 levels 35.6 / 23.8 and 47.9 / 38.5 streaming, of 3 levels 46.9 / 30.8
+  // and 54.3 / 40.9, of 4 57.7 / 38.8 and 58.5 / 41.8; 768 x 512 of 4 27.1 and 22.7 / 16.6 and 17.0
+  c->sweep_flat = c->stream_d && c->sweep_pref && nz <= (f64 ? 3 : 4);
   c->stream_shape = plan.shape;
   c->stream_nseg = plan.nseg;
   for (int d = 0; d < 2; ++d) c->stream_seg[d] = (const int*)(base + o_seg[d]);
@@ -1120,6 +1126,18 @@ int mr_divergence(mr_ctx* ctx, const void* u, const void* v, const void* w, doub
   return MR_OK;
 }
 
+// Whether a sequence on a flat grid can run as sweeps: their fields are allocated
+// on first use, which a capture forbids (it streams then).
+static bool flat_sweeps(mr_ctx* ctx, hipStream_t s) {
+  if (!ctx->sweep_flat) return false;
+  if (ctx->sweep_e[0] && ctx->sweep_e[1]) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) return false;
+  if (mr::ensure_sweep_buffers(ctx) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_cur, void* th_next,
                    const void* u, const void* v, const void* w, void* stream) {
   MR_CALL_RANGE();
@@ -1159,7 +1177,8 @@ int mr_scalar_steps(mr_ctx* ctx, int64_t n0, int32_t count, const void* th_prev,
     if (!outs[q] || outs[q] == l1 || outs[q] == l2) return MR_EINVAL;
   }
   hipStream_t s = as_stream(stream);
-  if (ctx->stream_d) {
+  const bool flat = flat_sweeps(ctx, s);
+  if (ctx->stream_d && !flat) {
     for (int32_t q = 0; q < count; ++q) {
       const void* a = q >= 2 ? outs[q - 2] : (q == 1 ? th_cur : thp);
       const void* b = q >= 1 ? outs[q - 1] : th_cur;
@@ -1238,7 +1257,8 @@ int mr_scalar_steps_backward(mr_ctx* ctx, int64_t n0, int32_t count, const void*
     if (!outs[q] || outs[q] == l1 || outs[q] == l2) return MR_EINVAL;
   }
   hipStream_t s = as_stream(stream);
-  if (ctx->stream_d) {
+  const bool flat = flat_sweeps(ctx, s);
+  if (ctx->stream_d && !flat) {
     for (int32_t q = 0; q < count; ++q) {
       const void* nxt = q >= 2 ? outs[q - 2] : (q == 1 ? mu_cur : mu_next);
       const void* cur = q >= 1 ? outs[q - 1] : mu_cur;
@@ -1346,7 +1366,7 @@ int mr_coarse_step(mr_ctx* ctx, int64_t n0, int32_t mt, const void* U0, const vo
     return MR_EINVAL;
   if (n0 == 0) p = c;
   hipStream_t s = as_stream(stream);
-  if (ctx->sweep_pref && !ctx->stream_d) {
+  if (ctx->sweep_pref && (!ctx->stream_d || flat_sweeps(ctx, s))) {
     // column sweeps: the kernel of sub-step i finishes theta^{n0+i-1} and
     // starts sub-step i on the velocity refined just before it (the velocity
     // at the start of the sub-step, fraction (i-1)/mt)

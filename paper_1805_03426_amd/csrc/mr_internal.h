@@ -215,6 +215,7 @@ struct mr_ctx {
   const int* stream_seg[2];        // per walk direction and segment: first position, end, walk start, walk end
   int sweep_shape;                 // column-sweep tile shape (index into kSweepShape)
   int sweep_pref;                  // run step sequences as column sweeps
+  int sweep_flat;                  // run them so although single steps stream
   int sweep_single;                // run single steps as a column sweep and its back substitution
   void* sweep_e[2];                // elimination values of two consecutive sweep steps (lazy)
   const double* areaw;             // [ny] hy_j (area = hx_i * hy_j, built in kernel)
@@ -258,6 +259,8 @@ hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_
 // writes no scalar; q > 0 writes theta^{n0+q} into th_out), then one back
 // substitution of the last step into out.
 bool sweep_supported(const mr_ctx* c);
+// Allocates the sweeps' elimination fields on the first call.
+hipError_t ensure_sweep_buffers(mr_ctx* c);
 hipError_t launch_sweep_step(mr_ctx* c, int64_t n0, int q, const void* lag, const void* src0,
                              void* th_out, const void* u, const void* v, const void* w, hipStream_t s);
 hipError_t launch_sweep_finish(mr_ctx* c, int64_t n0, int count, void* out, hipStream_t s);
