@@ -339,12 +339,17 @@ struct DissGrid {
 };
 DissGrid diss_grid(const mr_ctx* c) {
   DissGrid g;
-  // cells a lane: two in FP64, one in FP32 and on rows of one cell.  In us, 8e6
-  // cells: FP32 with one, two and four 450 x 177 x 100 22.5, 23.3, 25.4; 256 x 312 x
-  // 100 22.0, 21.3, 22.6; 40 x 2000 x 100 25.6, 35.1, 55.4 (four leave most lanes of
-  // a short row idle); 8 x 10000 x 100 72, 108, 205; FP64 with one and two 450 x 177
-  // x 100 26.2, 25.1; 256 x 312 x 100 26.1, 23.5; 40 x 2000 x 100 31.5, 36.3
-  g.V = c->precision == MR_FP64 && c->nx >= 2 ? 2 : 1;
+  // cells a lane: two in FP64; one in FP32, four on large grids whose rows fill the
+  // wider tiles; one on rows of one cell.  In us, 8e6 cells: FP32 with one, two and four
+  // 450 x 177 x 100 22.5, 23.3, 25.4; 256 x 312 x 100 22.0, 21.3, 22.6; 40 x 2000 x 100
+  // 25.6, 35.1, 55.4 (four leave most lanes of a short row idle); 8 x 10000 x 100 72, 108,
+  // 205; FP64 with one and two 450 x 177 x 100 26.2, 25.1; 256 x 312 x 100 26.1, 23.5; 40 x
+  // 2000 x 100 31.5, 36.3.  FP32, one and four, 2e7 cells and more: 1000 x 100 x 200 33.0,
+  // 34.6; 450 x 300 x 200 47.9, 42.5; 1024 x 1024 x 64 76.7, 69.2; 640 x 640 x 256 (rows
+  // of 2 1/2 tiles) 127, 130
+  const int wide = (c->nx + 4 * kWave - 1) / (4 * kWave) * 4 * kWave;
+  const bool four = (int64_t)c->nx * c->ny * c->nz >= 25000000 && 8 * (int64_t)c->nx >= 7 * (int64_t)wide;
+  g.V = c->precision != MR_FP64 ? (four ? 4 : 1) : c->nx >= 2 ? 2 : 1;
   g.nbx = (c->nx + kWave * g.V - 1) / (kWave * g.V);
   g.nby = (c->ny + kDissRows - 1) / kDissRows;
   const int64_t tiles = (int64_t)g.nbx * g.nby;
@@ -378,7 +383,7 @@ hipError_t launch_dissipation(mr_ctx* c, const void* th, double* out, hipStream_
                        g.idyc, c->idcz, c->nx, c->ny, c->nz, nbx, nby, kb, c->wx, c->wy, db, dtp, c->t_bot, c->t_top,
                        c->red);
   } else {
-    auto k = diss_partial<float, 1>;
+    auto k = d.V == 4 ? diss_partial<float, 4> : diss_partial<float, 1>;
     hipLaunchKernelGGL(k, dim3((unsigned)nb), block, 0, s, (const float*)th, c->hx64, c->areaw, c->hz64, g.idxc,
                        g.idyc, c->idcz, c->nx, c->ny, c->nz, nbx, nby, kb, c->wx, c->wy, db, dtp, c->t_bot, c->t_top,
                        c->red);
