@@ -522,26 +522,30 @@ int choose_chunks(int nz, int64_t tiles, int cus, bool f64, bool plain, bool ord
 //     than 8 wavefronts share a CU's registers;
 //   - the levels that the fullest CU walks, at what a wavefront's level takes of a
 //     busy CU (0.175 us, 0.092), five more a tile for its start and end;
-//   - the six values of every cell from memory (3.8 and 4.3 TB/s);
-// a tenth more where rows are not whole 64-byte lines, and for the variants.  In us,
-// estimated and timed: FP64 64 x 64 x 256 38 and 37, 128^3 22 and 25, 186^3 108 and
-// 102, 200^3 120 and 114, 320 x 320 x 64 85 and 77, 96 x 96 x 300 58 and 58, 256^3
-// 212 and 199; FP32 128^3 12 and 14, 150^3 33 and 35, 200^3 84 and 77, 64 x 64 x 512
-// 37 and 35, 256^3 96 and 96.
+//   - the six values of every cell (4.6 TB/s as long as they fit the Infinity Cache,
+//     then 3.8 in FP64 and 4.3 in FP32);
+// a tenth more where rows are not whole 64-byte lines, and for the variants (kl, kw).
+// In us, estimated and timed: FP64 64 x 64 x 256 38 and 37, 128^3 22 and 25, 186^3 108
+// and 102, 200^3 120 and 114, 320 x 320 x 64 85 and 77, 96 x 96 x 300 57 and 58, 256^3
+// 212 and 199; FP32 128^3 12 and 14, 150^3 33 and 35, 200^3 84 and 77, 64 x 64 x 512 37
+// and 35, 256^3 96 and 96; walls, fourth order and explicit z at 150 x 150 x 300 FP64
+// 149 and 145, FP32 79 and 85.
 double line_us(const Problem& P, const mr_desc* d, int64_t tiles, int cus, int L, int nch) {
   const bool f64 = d->precision == MR_FP64, ord4 = d->face_order == 4, expz = d->z_explicit > 0.0;
-  const double k = 1.0 + (ord4 && f64 ? 0.1 : 0.0) + (expz ? 0.15 : 0.0);
-  const double cells = (double)P.x.n * P.y.n * P.z.n, levels = k * nch * L;
+  const double kl = 1.0 + (ord4 ? 0.15 : 0.0) + (expz ? (f64 ? 0.1 : 0.4) : 0.0);
+  const double kw = 1.0 + (ord4 && f64 ? 0.15 : 0.0) + (expz ? (f64 ? 0.15 : 0.1) : 0.0);
+  const double levels = kw * nch * L;
   const double fill = std::min(1.0, (double)tiles / cus), rounds = (double)((tiles + cus - 1) / cus);
-  double chunk = f64 ? 3.0 + 1.1 * L * k : std::max(11.0, 3.0 + 0.58 * L * k);
+  double chunk = f64 ? 3.0 + 1.1 * L * kl : std::max(11.0, 3.0 + 0.58 * L * kl);
   if (nch > 8) {
     chunk *= 1.0 + (f64 ? 0.1 * (nch - 8) : P.sweep_ok ? 0.07 * (nch - 8) : 0.18 * std::min(nch - 8, 2));
     chunk *= 1.0 + 0.45 * std::min(fill, 0.6);
-    if ((ord4 || expz) && nch > 12) chunk *= 1.4;   // (128 registers a lane: these kernels spill)
+    if ((ord4 || expz) && nch > 12) chunk *= f64 ? 1.3 : 1.2;   // (128 registers a lane: these kernels spill)
   }
-  const double walked = tiles > cus ? (f64 ? 0.175 : 0.092) * rounds * (levels + 5.0 * k)
+  const double walked = tiles > cus ? (f64 ? 0.175 : 0.092) * rounds * (levels + 5.0 * kw)
                                     : levels * (f64 ? 0.115 + 0.06 * fill : 0.055 + 0.037 * fill);
-  const double mem = cells * (f64 ? 48.0 / 3.8e6 : 24.0 / 4.3e6);
+  const double bytes = (f64 ? 48.0 : 24.0) * P.x.n * P.y.n * P.z.n;
+  const double mem = bytes / (bytes < 2.4e8 ? 4.6e6 : f64 ? 3.8e6 : 4.3e6);
   return std::max({chunk, walked, mem}) * (P.x.n * (f64 ? 8 : 4) % 64 ? 1.1 : 1.0);
 }
 
@@ -918,13 +922,17 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     for (int d = mr::kStreamDepths; d > 0; --d)
       if (ahead <= mr::kStreamDepth[d - 1]) stream_d = d;
     if (stream_d) plan = mr::stream_plan(P.x.n, P.y.n, nz, f64, streamv, cus, stream_d - 1, before, after);
-    // the bounds above hold for look-aheads of up to 16 levels; a longer one is walked
-    // by every segment of a column, and takes a CU's registers: then the estimates
-    // decide.  One step in us, line solver and streaming, by the look-ahead: FP64
-    // 128^3 25 and 36 (16 levels), 46 (28), 44 (44), 57 (60), 192^3 96 and 87, 93, 97,
-    // 110, 64 x 64 x 256 37 and 23, 30, 38, 48; FP32 186^3 55 and 48, 65, 67, 78, 160 x
-    // 160 x 200 38 and 34, 44, 52, 61; with walls, FP64 96 x 96 x 160 30 and 52 (28)
-    if (stream_d == 0 || (nch > 0 && plan.us > line_us(P, desc, ltiles, cus, L, nch))) {
+    // the bounds above were set at short look-aheads; a longer one is walked by every
+    // segment of a column and takes a CU's registers: the estimates decide (up to 16
+    // levels ahead with a twentieth in favour of streaming, where both err least that
+    // way).  One step in us, line solver and streaming, by the look-ahead: FP64 128^3
+    // 25 and 36 (16 levels), 46 (28), 44 (44), 57 (60), 192^3 96 and 87, 93, 97, 110, 64
+    // x 64 x 256 37 and 23, 30, 38, 48; FP32 186^3 55 and 48, 65, 67, 78, 160 x 160 x 200
+    // 38 and 34, 44, 52, 61; with walls, FP64 96 x 96 x 160 30 and 52 (28).  Of 2246 steps
+    // timed in both forms over 73 grids and 7 look-aheads, 97 take 5% longer in the form
+    // so chosen (the worst 1.5 times)
+    const double favour = mr::kStreamDepth[std::max(stream_d - 1, 0)] <= 16 ? 1.05 : 1.0;
+    if (stream_d == 0 || (nch > 0 && plan.us > favour * line_us(P, desc, ltiles, cus, L, nch))) {
       streams = streamv = false;
       stream_d = 0;
       plan = mr::StreamPlan();
