@@ -182,15 +182,18 @@ int mr_divergence(mr_ctx* ctx, const void* u, const void* v, const void* w,
  * double for both precisions.  With step_method 0, x and y periodic with
  * uniform widths and the plain method, the step is one streaming kernel where
  * that is the fastest form (all but small grids: mr_init's rule on precision,
- * N_x, levels and cells) and the z system allows it: it back-
- * substitutes over a limited look-ahead, at most 60 levels, past which the
- * values left out enter the solution with a share below 7e-18 (FP64) or 1e-14
- * (FP32), less than the rounding of the stored type.  (A column that holds a
- * NaN or Inf therefore becomes non-finite from its look-ahead below, not whole,
- * in one step.)  Steps with side walls, fourth-order faces or an explicit z
- * share stream the same way on x and y of uniform widths from 2.5e6 cells on
- * (FP64 with an odd N_x: 4.5e6), and on grids of few columns taller than 128
- * levels.  Otherwise one fused line-solver kernel, or with
+ * N_x, levels, cells and look-ahead; mr_get_step_form tells) and the z system
+ * allows it: it back-substitutes over a limited look-ahead, at most 60 levels,
+ * past which the values left out enter the solution with a share below 7e-18
+ * (FP64) or 1e-14 (FP32), less than the rounding of the stored type.  Steps with
+ * side walls, fourth-order faces or an explicit z share stream the same way on x
+ * and y of uniform widths, by the same kind of rule (never the reverse ones).
+ * A NaN or Inf spreads to the same columns as in the line solver.  Within a column
+ * the line solver makes every level non-finite in one step; a streaming step those
+ * within the look-ahead on either side, and in the direction of its walk (up or down
+ * by turns; the variants up) those to the end of its z segment (the column is cut
+ * into up to 16), so that levels further away stay finite until a later step.
+ * Otherwise one fused line-solver kernel, or with
  * step_method 2 (and on columns taller than 640 levels) one column sweep and
  * its back substitution (see mr_scalar_steps). */
 int mr_scalar_step(mr_ctx* ctx, int64_t n, const void* th_prev, const void* th_cur, void* th_next,

@@ -869,31 +869,31 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     q.sht.tkb.assign(nz, 0.0);
   }
 
-  // the streaming step runs wherever it applies but on small grids where the
-  // line solver is faster: FP64 with copies into LDS of 4 bytes (odd N_x): 127^3
-  // 54 us against 30, 175^3 86 against 99; FP64 columns of at most 64 levels in
-  // one round of tiles: 64^3 14.8 us against 13.3, 128 x 128 x 64 19.7 against
-  // 16.1 (but 128^3 27.0 against 26.2, 160 x 160 x 64 21.5 against 24.4, 60 x 60
-  // x 128 18.4 against 24.4); FP32 columns of at most 128 levels in one round:
-  // 128^3 17.9 against 16.1 (but 64 x 64 x 150 16.8 against 18.4, 64 x 64 x 500
-  // 26.4 against 36.5, 128 x 128 x 256 27.4 against 26.7, reverse 26.8 against
-  // 28.8), and FP32 grids of several rounds below 2.5e6 cells (150^3 31.3 against
-  // 36.4, 200 x 200 x 100 28.2 against 48.5)
+  // the streaming step runs where it applies but on small grids where the line solver
+  // is faster; the lines lie where the two are level at short look-aheads (longer ones:
+  // below).  One step in us, streaming against line solver, 13 levels ahead:
+  //   FP64 with copies into LDS of 4 bytes (odd N_x), 4.5e6 cells: 187 x 187 x 100 60 and
+  //     65, 255 x 255 x 64 52 and 54, 127^3 48 and 28; 255^3 194 and 278;
+  //   FP64 else, one round of tiles, 64 levels: 64^3 18 and 12, 128 x 128 x 64 25 and 15;
+  //     64 x 64 x 96 18 and 20, 64 x 64 x 128 19 and 21;
+  //   FP32, one round, 128 levels: 64 x 64 x 128 14 and 12, 128^3 22 and 14; 64 x 64 x 256
+  //     18 and 20, 64 x 64 x 512 26 and 35;
+  //   FP32, several rounds, 2.5e6 cells: 160 x 160 x 96 24 and 18, 192 x 192 x 64 24 and
+  //     18, 200 x 200 x 60 (2.4e6) 24 and 25; 300 x 280 x 30 (2.52e6) 19 and 21, 186 x 186
+  //     x 100 32 and 37
   const bool one_round = ltiles <= cus;
   const int64_t cells = (int64_t)P.x.n * P.y.n * nz;
   bool streams = P.sweep_ok && desc->step_method == 0 &&
                  (nch == 0 || cells >= 4500000 ||
                   (f64 ? P.x.n % 2 == 0 && !(one_round && nz <= 64) : (one_round ? nz > 128 : cells >= 2500000)));
-  // the variants' forward step streams (x and y of uniform widths) on grids of
-  // 2.5e6 cells and more (FP64 with 4-byte copies 4.5e6) and on tall columns in
-  // one round of tiles.  One step in us, line solver against streaming, with walls,
-  // fourth order and explicit z / with walls alone: FP64 186^3 132 and 76 / 105
-  // and 75, 250^3 270 and 153 / 234 and 149, 300 x 280 x 30 44 and 31 / 39 and 31,
-  // 64 x 64 x 256 56 and 28 / 41 and 27, 128^3 33 and 31 / 27 and 31, 160 x 160 x
-  // 64 30 and 26 / 25 and 26, 64^3 19 and 17 / 14 and 17; FP32 186^3 77 and 42 /
-  // 53 and 42, 300 x 280 x 30 24 and 23 / 21 and 23, 160 x 160 x 64 20 and 19 / 16
-  // and 18; FP64 odd: 187^3 134 and 82 / 106 and 81, 301 x 280 x 30 44 and 45 / 39
-  // and 45
+  // the variants' forward step streams (x and y of uniform widths) on grids of 2.5e6
+  // cells and more (FP64 with 4-byte copies 4.5e6) and on tall columns in one round of
+  // tiles.  Streaming against line solver, with walls, fourth order and explicit z / with
+  // walls alone: FP64 186^3 75 and 126 / 78 and 100, 256^3 184 and 232 / 180 and 200, 300 x
+  // 280 x 30 29 and 39 / 28 and 36, 64 x 64 x 256 27 and 52 / 29 and 38; 160 x 160 x 64 33
+  // and 27 / 33 and 23, 64^3 22 and 15 / 27 and 12; odd 255^3 183 and 298 / 167 and 267;
+  // FP32 186^3 45 and 76 / 47 and 50, 300 x 280 x 30 20 and 20 / 19 and 19, 64 x 64 x 256 21
+  // and 34 / 20 and 22; 160 x 160 x 64 22 and 18 / 22 and 14
   const bool copies4 = f64 && P.x.n % 2 != 0;
   bool streamv = !P.sweep_ok && desc->step_method == 0 && nch > 0 && uniform_axis(P.x) && uniform_axis(P.y) &&
                  (cells >= (copies4 ? 4500000 : 2500000) || (one_round && nz > 128 && !copies4));

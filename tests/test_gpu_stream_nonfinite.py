@@ -69,3 +69,28 @@ def test_columns_reached(variant, prec, offset):
                     assert err <= (1e-13 if prec == "fp64" else 1e-5), err
                     if field in ("cur", "prev"):
                         assert got_bad[k, j, i]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("variant", ["plain", "all"])
+def test_levels_reached(variant, prec):
+    """A level that is not finite takes those within the look-ahead along on both
+    sides (13 levels at r = 0.05; at least 8 here), walking up and down, and in the
+    reverse step."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    with _ctx("auto", prec, VARIANTS[variant]) as ctx:
+        assert ctx.step_form() == "stream"
+        cur, prev = (_field(ctx.shape_cell, ctx.dtype, 2.0, 0, gen) for _ in range(2))
+        u, v = (_field(ctx.shape_cell, ctx.dtype, 0.3, 0, gen) for _ in range(2))
+        w = torch.zeros(ctx.shape_w, dtype=ctx.dtype, device="cuda")
+        out = ctx.empty(ctx.shape_cell)
+        for k in (0, 7, 20, 37, 38, 75, 150, 222, 299):
+            cur[k, 5, 18] = float("nan")
+            calls = [lambda: ctx.scalar_step(2, prev, cur, out, u, v, w), lambda: ctx.scalar_step(3, prev, cur, out, u, v, w)]
+            if variant == "plain":
+                calls += [lambda n=n: ctx.scalar_step_backward(n, prev, cur, None, out, u, v, w) for n in (2, 3)]
+            for q, call in enumerate(calls):
+                print("case levels", variant, prec, k, q, flush=True)
+                call()
+                assert not torch.isfinite(out[max(0, k - 8):k + 9, 5, 18]).any()
+            cur[k, 5, 18] = 0.0
