@@ -524,12 +524,13 @@ int choose_chunks(int nz, int64_t tiles, int cus, bool f64, bool plain, bool ord
 //     busy CU (0.175 us, 0.092), five more a tile for its start and end;
 //   - the six values of every cell (4.6 TB/s as long as they fit the Infinity Cache,
 //     then 3.8 in FP64 and 4.3 in FP32);
-// a tenth more where rows are not whole 64-byte lines, and for the variants (kl, kw).
+// a tenth more where rows are not whole 64-byte lines (not the FP32 variants), and
+// more for the variants (kl, kw).
 // In us, estimated and timed: FP64 64 x 64 x 256 38 and 37, 128^3 22 and 25, 186^3 108
 // and 102, 200^3 120 and 114, 320 x 320 x 64 85 and 77, 96 x 96 x 300 57 and 58, 256^3
 // 212 and 199; FP32 128^3 12 and 14, 150^3 33 and 35, 200^3 84 and 77, 64 x 64 x 512 37
 // and 35, 256^3 96 and 96; walls, fourth order and explicit z at 150 x 150 x 300 FP64
-// 149 and 145, FP32 79 and 85.
+// 149 and 145, FP32 72 and 85; walls at 186 x 186 x 100 FP32 37 and 34.
 double line_us(const Problem& P, const mr_desc* d, int64_t tiles, int cus, int L, int nch) {
   const bool f64 = d->precision == MR_FP64, ord4 = d->face_order == 4, expz = d->z_explicit > 0.0;
   const double kl = 1.0 + (ord4 ? 0.15 : 0.0) + (expz ? (f64 ? 0.1 : 0.4) : 0.0);
@@ -546,7 +547,7 @@ double line_us(const Problem& P, const mr_desc* d, int64_t tiles, int cus, int L
                                     : levels * (f64 ? 0.115 + 0.06 * fill : 0.055 + 0.037 * fill);
   const double bytes = (f64 ? 48.0 : 24.0) * P.x.n * P.y.n * P.z.n;
   const double mem = bytes / (bytes < 2.4e8 ? 4.6e6 : f64 ? 3.8e6 : 4.3e6);
-  return std::max({chunk, walked, mem}) * (P.x.n * (f64 ? 8 : 4) % 64 ? 1.1 : 1.0);
+  return std::max({chunk, walked, mem}) * (P.x.n * (f64 ? 8 : 4) % 64 && (f64 || P.sweep_ok) ? 1.1 : 1.0);
 }
 
 // Byte buffer that hands out 256-byte aligned slots.
@@ -929,7 +930,7 @@ int mr_init(const mr_desc* desc, mr_ctx** out) {
     // 25 and 36 (16 levels), 46 (28), 44 (44), 57 (60), 192^3 96 and 87, 93, 97, 110, 64
     // x 64 x 256 37 and 23, 30, 38, 48; FP32 186^3 55 and 48, 65, 67, 78, 160 x 160 x 200
     // 38 and 34, 44, 52, 61; with walls, FP64 96 x 96 x 160 30 and 52 (28).  Of 2246 steps
-    // timed in both forms over 73 grids and 7 look-aheads, 97 take 5% longer in the form
+    // timed in both forms over 73 grids and 7 look-aheads, 88 take 5% longer in the form
     // so chosen (the worst 1.5 times)
     const double favour = mr::kStreamDepth[std::max(stream_d - 1, 0)] <= 16 ? 1.05 : 1.0;
     if (stream_d == 0 || (nch > 0 && plan.us > favour * line_us(P, desc, ltiles, cus, L, nch))) {
