@@ -78,7 +78,7 @@ def _variant(order, nc, walls, wz, **kw):
 def test_streaming_variants(order, walls, wz, nc):
     for prec, tol in (("fp64", FP64_TOL), ("fp32", FP32_TOL)):
         print("case form reach variant", order, walls, wz, nc, prec, flush=True)
-        c = _variant(order, nc, walls, wz, precision=prec, dt=2e-5, n_avg=3)
+        c = _variant(order, nc, walls, wz, precision=prec, dt=2e-6, n_avg=3)   # (short look-aheads)
         with c.ctx() as ctx:
             _streams(ctx, CALLS[:2])
         _steps(c, 4, tol)
@@ -89,7 +89,7 @@ def test_streaming_variants(order, walls, wz, nc):
 @pytest.mark.parametrize("order,walls,wz", VARIANTS)
 def test_canaries_streaming_variants(order, walls, wz, prec, offset):
     print("case canaries streaming variants", order, walls, wz, prec, offset, flush=True)
-    kw = dict(precision=prec, n_avg=3, dt=2e-5)
+    kw = dict(precision=prec, n_avg=3, dt=2e-6)   # (short look-aheads)
     nc, m = (35, 5, 160), (2, 2, 2)   # 70 x 10 x 320
     c = Case4(nc, m, walls, z_explicit=wz, **kw) if order == 4 else _Variant(nc, walls, wz, m=m, **kw)
     c.th0 = inputs.theta_initial(c.zf, c.g.x.n, c.g.y.n, noise=0.1, seed=2)
