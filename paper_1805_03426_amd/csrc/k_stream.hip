@@ -25,10 +25,11 @@ extern template hipError_t launch_stream_var<float>(int, int, dim3, const VarArg
 //   - the levels of a walk times what a level takes a CU that holds one
 //     workgroup, or as many as the fullest CU gets.
 // Timed, for instance (128 x 4 columns: 256^3 in FP64, 144 us with 2 segments,
-// one workgroup for each of 256 CUs; 185 us with 1, 180 with 3, half of the CUs
+// one workgroup for each of 256 CUs; 189 us with 1, 177 with 3, half of the CUs
 // idle or a second round for half of them).  400^3 FP64: 256 x 4 and 1 segment
-// 587 us, 128 x 4 692; 576^3 FP64: 192 x 4 1.83 ms, 256 x 4 2.06; 450 x 300 x
-// 200 FP32: 192 x 4 154 us, 128 x 4 183 (300 workgroups on 256 CUs).
+// 602 us, 128 x 4 702; 576^3 FP64: 192 x 4 1.87 ms, 256 x 4 2.09; 450 x 300 x
+// 200 FP32, 1 segment: 192 x 4 155 us, 128 x 4 190 (300 workgroups on 256 CUs; at
+// a reach of few levels the model takes 2 segments, 2% ahead by its figures: 171).
 // The estimate that goes with the plan (us) takes a level's time on a CU that holds
 // one workgroup (alone_us), or several, from steps timed at 66 grids and four
 // look-aheads each (medians by shape); the choice among plans leaves the 64-column
@@ -36,7 +37,7 @@ extern template hipError_t launch_stream_var<float>(int, int, dim3, const VarArg
 // bytes take 1.6 times as long (FP64) and 1.1 (FP32).  Look-aheads of 60 levels leave
 // a CU two workgroups of 4 wavefronts at a time.
 // Variants (walls, fourth order, explicit z): 186^3 FP64 192 x 4 columns and 4
-// segments 66 us, 3 segments 76, 64 x 4 and 3 segments 68; 128 x 4 and 5, 82.
+// segments 72 us, 3 segments 77, 64 x 4 and 3 segments 68; 128 x 4 and 5, 85.
 StreamPlan stream_plan(int nx, int ny, int nz, bool f64, bool variant, int cus, int depth, const std::vector<int> (&before)[2],
                        const std::vector<int> (&after)[2]) {
   struct Shape {
@@ -174,7 +175,7 @@ hipError_t fwd_t(mr_ctx* c, int64_t n, int q, const void* thp, const void* thc, 
 // diffusion of step n+1 on mu^{n+1} (zero weights without one), the transposed
 // system of step n-1.  Step 0: no system (the derivative with respect to theta^0),
 // and the start-up step's own diffusion.  In us, line solver and this: 256^3 FP32
-// 103 and 88, 1024 x 1024 x 512 FP32 4157 and 2417, FP64 9101 and 5099.
+// 103 and 84, 1024 x 1024 x 512 FP32 4016 and 2451, FP64 8352 and 5172.
 template <typename T>
 hipError_t bwd_t(mr_ctx* c, int64_t n, const void* mun, const void* muc, void* out, const void* u, const void* v,
                  const void* w, hipStream_t s) {

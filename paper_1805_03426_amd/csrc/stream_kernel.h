@@ -28,12 +28,13 @@
 // worked on (no registers hold loads in flight, which leaves them to the
 // elimination values), and one barrier per level hands it over.  x, y
 // neighbours then come from LDS.  Timed per step at 1024 x 1024 x 512 on
-// 256 x 4 tiles: 4.97 ms in FP64 (5.2 TB/s of the 6 values per cell; a copy of
-// this size reaches 5.1-5.4) and 2.39 ms in FP32 (5.4 TB/s), against 6.0 and
-// 2.69 ms for the column sweeps, whose elimination values go through memory.
-// The same walk with loads into registers and neighbours from the cache took
-// 6.0 and 3.2 ms: 26% (FP64) and 62% (FP32) more lines came from memory than
-// the five fields have, because the wavefronts drifted apart.
+// 256 x 4 tiles: 5.18 ms in FP64 (4.97 TB/s of the 6 values per cell; a copy of
+// this size reaches 5.3) and 2.44 ms in FP32 (5.3 TB/s), against 6.24 and 2.75 ms
+// for the column sweeps, whose elimination values go through memory, and 8.24 and
+// 3.89 for the line solver; the reverse step 5.17 and 2.45, 6.30 and 2.77, 8.35 and
+// 4.02.  The same walk with loads into registers and neighbours from the cache took
+// a fifth (FP64) and a third (FP32) longer than this: 26% and 62% more lines came
+// from memory than the five fields have, because the wavefronts drifted apart.
 #pragma once
 
 #include <string.h>

@@ -19,13 +19,15 @@
 //   - the walk always goes up, and the weights hold registers: workgroups of at
 //     most 12 wavefronts.
 // Walls and the explicit z share are no template parameters: they cost little.
-// On grids that fill the GPU it is bound by the bytes (400 x 300 x 200 FP64: 294 us,
-// 3.9 TB/s of the 6 values per cell; the plain step 275), on small ones by a
+// On grids that fill the GPU it is bound by the bytes (400 x 300 x 200: FP64 267 us,
+// 4.3 TB/s of the 6 values per cell, the line solver 464; FP32 158 and 304; with
+// walls alone 258 and 377, 155 and 186), on small ones by a
 // level's chain from barrier to barrier (0.6 us with one wavefront per SIMD, 0.9
 // with three).  The table row of a level is read at its start, from lines that a
 // block's first level has brought into the scalar cache: rows carried in scalar
 // registers a level ahead spilled them into vector lanes (140 vector instructions
-// a level instead of 66, 186^3 FP64 90 us instead of 66; the line solver: 133).
+// a level instead of 66, a third more time at 186^3 FP64: 72 us now, the line
+// solver 135).
 #pragma once
 
 #include "stream_kernel.h"
