@@ -392,8 +392,9 @@ hipError_t launch_shape(int shape, int depth, dim3 grid, const StreamArgs<T>& a,
 }
 
 // 16-byte copies where every row of every field starts on 16 bytes, else
-// 4-byte ones (four times the copies; at 1024 x 1024 x 512 they take the same
-// time, at 256^3 13% more in FP64).
+// 4-byte ones (four times the copies: at 1024 x 1024 x 512 up to 5% more
+// time, at 256^3 18% more in FP64 and 12% in FP32; on small grids, bound by a
+// level's chain, up to 60%).
 template <typename T, bool REV>
 hipError_t launch_stream(int shape, int depth, dim3 grid, const StreamArgs<T>& a, hipStream_t s) {
   const uintptr_t p = (uintptr_t)a.f | (uintptr_t)a.p | (uintptr_t)a.u | (uintptr_t)a.v | (uintptr_t)a.w;
